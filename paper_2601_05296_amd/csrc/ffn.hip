@@ -105,8 +105,7 @@ g1_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
     SlotTile t;
     const int NT = (f + C::BN - 1) / C::BN;
     if (!find_slot_tile<C::THREADS>(reinterpret_cast<int*>(lds), offsets, E, C::BM, NT,
-                                    xcd_remap(blockIdx.x, gridDim.x), C::BN,
-                                    t, RASTER_GM))
+                                    blockIdx.x, C::BN, t, RASTER_GM))
         return;
     rs::GatherKC<C, C::BM> la;
     la.init(x, d, eti + t.off + t.m0, t.mrows);
@@ -258,8 +257,7 @@ g2_kernel(const bf16_t* __restrict__ H, const bf16_t* __restrict__ w2,
     SlotTile t;
     const int NT = (ncols + C::BN - 1) / C::BN;
     if (!find_slot_tile<C::THREADS>(reinterpret_cast<int*>(lds), offsets, E, C::BM, NT,
-                                    xcd_remap(blockIdx.x, gridDim.x), C::BN,
-                                    t, RASTER_GM))
+                                    blockIdx.x, C::BN, t, RASTER_GM))
         return;
     rs::DenseKC2<C, C::BM> la;
     la.init(H, H, f, (int64_t)t.off + t.m0, t.mrows, f);
@@ -340,7 +338,7 @@ g2h_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
     SlotTile t;
     const int NT = (ncols + C::BN - 1) / C::BN;
     if (!find_slot_tile<C::THREADS>(reinterpret_cast<int*>(lds), offsets, E, C::BM, NT,
-                                        xcd_remap(blockIdx.x, gridDim.x), C::BN, t, RASTER_GM))
+                                    blockIdx.x, C::BN, t, RASTER_GM))
         return;
     HKC<ACT, C, C::BM> la;
     la.init(A, B, f, (int64_t)t.off + t.m0, t.mrows);
@@ -369,8 +367,7 @@ g4_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w2,
     SlotTile t;
     const int NT = (f + C::BN - 1) / C::BN;
     if (!find_slot_tile<C::THREADS>(reinterpret_cast<int*>(lds), offsets, E, C::BM, NT,
-                                    xcd_remap(blockIdx.x, gridDim.x), C::BN,
-                                    t, RASTER_GM))
+                                    blockIdx.x, C::BN, t, RASTER_GM))
         return;
     rs::GatherKC<C, C::BM> la;
     la.init(dy, d, eti + t.off + t.m0, t.mrows);
@@ -748,8 +745,7 @@ g6_kernel(const bf16_t* __restrict__ dA, const bf16_t* __restrict__ dB,
     SlotTile t;
     const int NT = (ncols + C::BN - 1) / C::BN;
     if (!find_slot_tile<C::THREADS>(reinterpret_cast<int*>(lds), offsets, E, C::BM, NT,
-                                    xcd_remap(blockIdx.x, gridDim.x), C::BN,
-                                    t, RASTER_GM))
+                                    blockIdx.x, C::BN, t, RASTER_GM))
         return;
     rs::DenseKC2<C, C::BM> la;
     la.init(dA, dB, f, (int64_t)t.off + t.m0, t.mrows, f);

@@ -216,7 +216,12 @@ inline int wgrad_grid(int E, int MT, int NT) { return E * 8 * ((MT * NT + 7) / 8
 // inside a group: the workgroups that run at the same time on one XCD then
 // cover a GM x (32 / GM) block of tiles, which share both their row panels
 // and their weight panels in that XCD's L2 (an expert's last, narrower group
-// holds its remaining M tiles). Every thread of the block must call this;
+// holds its remaining M tiles). The block ids [0, total) of the tiles that
+// exist are renumbered over the XCDs (xcd_remap), `total` being the scan's own
+// sum: the grid is the worst case of one partial tile per expert, and dealing
+// out contiguous ranges of that grid left the last XCDs with padding while the
+// first had more than their share (one token, E = 64, k = 6: 66 tiles, all on
+// one XCD: layer forward 194 us, now 117; T = 1021 fwd + bwd 1281 -> 1156 us). Every thread of the block must call this;
 // `sh` is 8 ints of LDS, free on entry and again on return. Returns false past
 // the last tile.
 struct SlotTile {
@@ -242,8 +247,10 @@ __device__ bool find_slot_tile(int* sh, const int32_t* __restrict__ offsets, int
     // the waves before (E <= 256: four waves)
     const int inc = wave_incl_scan(tiles);
     if (wv < 4 && lane == WAVE - 1) sh[wv] = inc;
-    if (tid == 0) sh[4] = -1;
     __syncthreads();
+    const int total = sh[0] + sh[1] + sh[2] + sh[3];
+    if (bid >= total) return false;
+    bid = xcd_remap(bid, total);
     if (tid < E) {
         int end = inc;
         for (int w = 0; w < wv; ++w) end += sh[w];
@@ -255,7 +262,6 @@ __device__ bool find_slot_tile(int* sh, const int32_t* __restrict__ offsets, int
     off = sh[6];
     cnt = sh[7];
     __syncthreads();
-    if (e < 0) return false;
     const int nmt = (cnt + BM - 1) / BM;
     const int gm = GM > 0 ? GM : nmt;         // M tiles per group
     const int full = nmt / gm * gm;           // M tiles in whole groups
