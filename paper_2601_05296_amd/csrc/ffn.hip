@@ -38,6 +38,7 @@
 //
 // The float32 debug mode uses plain one-output-per-thread kernels.
 #include "common.hpp"
+#include "ffn_epi.hpp"
 #include "gemm.hpp"
 #include "gemm_rs.hpp"
 #include "launch.hpp"
@@ -53,30 +54,6 @@ using RD = rs::Cfg<256, 128, 2, 4, 2>;  // G1, G5
 using RS = rs::Cfg<256, 256, 2, 4, 1>;  // G2, G3, G6
 constexpr int RASTER_GM = 4;            // M tiles per raster group (find_slot_tile)
 
-// ============================ epilogue helpers ===================================
-
-__device__ __forceinline__ void store4_bf16(bf16_t* p, float a, float b, float c, float d) {
-    *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf2(a, b), pack_bf2(c, d));
-}
-__device__ __forceinline__ float silu_bf(float a) { return a * sigmoidf_(a); }
-
-// Expert activation: SwiGLU (gated, Section 5.1) or the non-gated SiLU / ReLU
-// experts of Section 2.2, E(x) = W2 act(W1 x), whose only saved activation is
-// A = x W1. ReLU'(0) is taken as 0.
-enum : int { ACT_SWIGLU = 0, ACT_SILU = 1, ACT_RELU = 2 };
-template <int ACT>
-__device__ __forceinline__ float act_f(float a) {
-    if constexpr (ACT == ACT_RELU) return a > 0.f ? a : 0.f;
-    else return a * sigmoidf_(a);
-}
-template <int ACT>
-__device__ __forceinline__ float act_d(float a) {
-    if constexpr (ACT == ACT_RELU) return a > 0.f ? 1.f : 0.f;
-    else {
-        const float sg = sigmoidf_(a);
-        return sg * (1.0f + a * (1.0f - sg));
-    }
-}
 // tile configuration of the first-layer and dW1 GEMMs: two right operands
 // when gated (W1|W3, dA|dB), one otherwise
 template <int ACT> using CFirst = std::conditional_t<ACT == ACT_SWIGLU, RD, RS>;
@@ -86,7 +63,6 @@ template <int ACT> using CFirst = std::conditional_t<ACT == ACT_SWIGLU, RD, RS>;
 // as much vector-ALU time per slice as the slice's MFMAs take).
 using RHW = rs::Cfg<128, 512, 2, 4, 1>;
 static_assert(RD::THREADS == RS::THREADS && RD::LDS == RS::LDS, "RD and RS launch alike");
-__device__ __forceinline__ void store8_bf16(bf16_t* p, const float (&v)[8]) { st16(p, pack8(v)); }
 
 // ============================ kernels ==============================================
 
@@ -120,127 +96,7 @@ g1_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
         rs::NoLoader nl;
         rs::mainloop<C>(la, lb0, nl, d / rs::KS, lds, acc);
     }
-    WaveCoord<C> wc;
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i) {
-        const int m = wc.row(i);
-        if (m >= t.mrows) continue;
-        const int64_t s = (int64_t)t.off + t.m0 + m;
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) {
-            float va[2][8], vb[2][8];
-            frag_cols8(acc[0][i][j], va);
-            if constexpr (ACT == ACT_SWIGLU) frag_cols8(acc[1][i][j], vb);
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int n = t.n0 + wc.col8(j, p);
-                if (n >= f) continue;
-                float a[8], b[8], h[8];
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    a[r] = bf2f(f2bf(va[p][r]));
-                    if constexpr (ACT == ACT_SWIGLU) {
-                        b[r] = bf2f(f2bf(vb[p][r]));
-                        h[r] = silu_bf(a[r]) * b[r];
-                    } else {
-                        h[r] = act_f<ACT>(a[r]);
-                    }
-                }
-                store8_bf16(A + s * f + n, a);
-                if constexpr (ACT == ACT_SWIGLU) store8_bf16(B + s * f + n, b);
-                if (H) store8_bf16(H + s * f + n, h);
-            }
-        }
-    }
-}
-
-// Output rows of a slot tile (G2, G6), columns n < ncols of the tile's strip:
-// slot row s goes to row s of O, rows ldo apart.
-template <class C>
-__device__ __forceinline__ void slot_rows_out(const rs::Acc<C>& acc, const SlotTile& t,
-                                              int ncols, int64_t ldo, bf16_t* __restrict__ O) {
-    WaveCoord<C> wc;
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i) {
-        const int m = wc.row(i);
-        if (m >= t.mrows) continue;
-        const int64_t s = (int64_t)t.off + t.m0 + m;
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) {
-            float v[2][8];
-            frag_cols8(acc[0][i][j], v);
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int n = t.n0 + wc.col8(j, p);
-                if (n < ncols) store8_bf16(O + s * ldo + n, v[p]);
-            }
-        }
-    }
-}
-
-// The combine folded into the epilogue (Section 3.1): slot row s of the tile,
-// times gs[s] (1 when gs is null), rounded to bf16, is added into row tok[s]
-// of O (rows ldo apart) by packed-bf16 atomics, so that O receives the sum
-// over a token's slots in whatever order the tiles finish. The tile goes
-// through LDS first (free once the main loop is done), so that each atomic
-// instruction of a wave covers 256 contiguous bytes of one row: 64 lanes, two
-// columns each (straight from the fragments, a wave's atomics would touch 32
-// rows 16 bytes apiece). 16-byte chunks are XOR-swizzled by row, so that both
-// the fragment-ordered writes and the row-ordered reads are free of bank
-// conflicts.
-template <class C>
-__device__ __forceinline__ void slot_rows_scatter(const rs::Acc<C>& acc, const SlotTile& t,
-                                                  int ncols, int64_t ldo,
-                                                  bf16_t* __restrict__ O,
-                                                  const int32_t* __restrict__ tok,
-                                                  const float* __restrict__ gs, char* lds) {
-    constexpr int RB = C::BN * 2;      // bytes per tile row in LDS
-    constexpr int CPR = C::BN / 8;     // 16-byte chunks per row
-    static_assert(C::BM * RB <= C::LDS && CPR >= 32 && C::BN % 128 == 0, "scatter staging");
-    const WaveCoord<C> wc;
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i) {
-        const int m = wc.row(i);
-        const float g = (gs && m < t.mrows) ? gs[(int64_t)t.off + t.m0 + m] : 1.0f;
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) {
-            float v[2][8];
-            frag_cols8(acc[0][i][j], v);
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-#pragma unroll
-                for (int r = 0; r < 8; ++r) v[p][r] *= g;
-                const int chunk = (wc.col8(j, p) >> 3) ^ (m & 31);
-                *reinterpret_cast<uint4*>(lds + m * RB + chunk * 16) = pack8(v[p]);
-            }
-        }
-    }
-    __syncthreads();
-    const int wv = wave_id();
-    const int rows = min(C::BM, t.mrows);
-    for (int r = wv; r < rows; r += C::NW) {
-        bf16_t* dst = O + (int64_t)tok[(int64_t)t.off + t.m0 + r] * ldo + t.n0;
-#pragma unroll
-        for (int c = 0; c < C::BN / 128; ++c) {
-            const int col = c * 128 + 2 * wc.lane;
-            if (t.n0 + col >= ncols) continue;
-            const int chunk = (col >> 3) ^ (r & 31);
-            const uint32_t v =
-                *reinterpret_cast<const uint32_t*>(lds + r * RB + chunk * 16 + (col & 7) * 2);
-            __builtin_amdgcn_global_atomic_fadd_v2bf16(reinterpret_cast<bf16x2_t*>(dst + col),
-                                                       __builtin_bit_cast(bf16x2_t, v));
-        }
-    }
-}
-
-// slot rows out, plain or (SCATTER) added into the token rows
-template <bool SCATTER, class C>
-__device__ __forceinline__ void slot_rows(const rs::Acc<C>& acc, const SlotTile& t, int ncols,
-                                          int64_t ldo, bf16_t* __restrict__ O,
-                                          const int32_t* __restrict__ tok,
-                                          const float* __restrict__ gs, char* lds) {
-    if constexpr (SCATTER) slot_rows_scatter<C>(acc, t, ncols, ldo, O, tok, gs, lds);
-    else slot_rows_out<C>(acc, t, ncols, ldo, O);
+    first_rows_out<ACT, C>(acc, t, f, A, B, H);
 }
 
 // G2: O = H W2[e], output columns [n_base, n_base + ncols) of W2 into columns
@@ -269,18 +125,6 @@ g2_kernel(const bf16_t* __restrict__ H, const bf16_t* __restrict__ w2,
     slot_rows<SCATTER, C>(acc, t, ncols, ldo, O, tok, gs, lds);
 }
 
-// h of one element from its (bf16-valued) A and B: the arithmetic of G1's
-// epilogue, on the same values, so the result is bit-identical to the
-// buffered h. Non-gated: act(A), B unused. With a gate g: g * h, the
-// arithmetic of G4's epilogue for the dW2 GEMM's operand.
-template <int ACT, bool GATE>
-__device__ __forceinline__ float h_one(float a, float b, float g) {
-    float h;
-    if constexpr (ACT == ACT_SWIGLU) h = silu_bf(a) * b;
-    else h = act_f<ACT>(a);
-    if constexpr (GATE) h = g * h;
-    return h;
-}
 // h of element pair dword p of (va, vb) as two transform pieces of one element
 // each: piece 2p forms the low element into hl, piece 2p+1 the high one and
 // packs the pair in place of va's dword (pieces of one element keep the
@@ -483,21 +327,7 @@ g4_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w2,
                     unpack8(*reinterpret_cast<const uint4*>(rowB + off), b);
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
-                    const float u = u8[p][r];
-                    const float dh = g * u;
-                    float h;
-                    if constexpr (ACT == ACT_SWIGLU) {
-                        const float sg = sigmoidf_(a[r]);
-                        const float sl = a[r] * sg;
-                        h = sl * b[r];
-                        da[r] = dh * b[r] * sg * (1.0f + a[r] * (1.0f - sg));
-                        db[r] = dh * sl;
-                    } else {
-                        h = act_f<ACT>(a[r]);
-                        da[r] = dh * act_d<ACT>(a[r]);
-                    }
-                    dg += n < f ? u * h : 0.f;
-                    hg[r] = g * h;
+                    dact_one<ACT>(u8[p][r], a[r], b[r], g, n < f, da[r], db[r], hg[r], dg);
                 }
                 *reinterpret_cast<uint4*>(rowA + off) = pack8(da);
                 if constexpr (ACT == ACT_SWIGLU) *reinterpret_cast<uint4*>(rowB + off) = pack8(db);
@@ -951,6 +781,62 @@ inline unsigned slot_grid(int64_t S, int E, int BM, int NT) {
 }
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
+// ---- which core runs a row-wise GEMM (ffn_small.hip) ----
+// The choice rests on the sizes alone (the host does not see the routing): r =
+// S / E rows per expert, and the number of tiles a launch would have, estimated
+// as one per expert that can have a slot, or a third of a tile of padding per
+// expert once they fill. Measured on one MI355X, kernel times in us as (256-row
+// core, small core):
+//  - r <= 112: 64-row tiles up to r = 40, then 128-row tiles. First layer, E = 64,
+//    d = 2048, f = 1408: r = 4 (149, 124), 48 (152, 136), 96 (159, 148); r = 141
+//    (201, 216). E = 128, d = f = 2880: r = 9 (808, 696), 64 (856, 792). dh
+//    GEMM there: r = 96 (127, 103), 9 (526, 374); E = 8, d = 4096, f = 14336:
+//    r = 112 (219, 202), 150 (230, 315).
+//  - the second GEMM and the dX GEMM (N = d, K = f or 2f) leave the chip half
+//    idle in 256 x 256 tiles when the experts are few: 128-row tiles then up to
+//    r = 256 (dX, E = 8, d = 4096, f = 14336: r = 32 (487, 332), 150 (538, 447);
+//    E = 16, d = 1024, f = 4096: r = 200 (153, 89)).
+//  - columns: the widest tiles if they give 192 workgroups; the dX and second
+//    GEMMs, with longer K and fewer columns, take 128 columns while those tiles
+//    run in one round (E = 8: 330 against 400 of the wide ones) and 64 while
+//    those do (E = 16: 55 against 65 and 95).
+//  - h formed on load: the 128 x 512 core (RHW) forms each h once per 512
+//    columns and reads at the memory rate from about 100 workgroups on (E = 64,
+//    r = 4: 68, the small tiles 68 to 113); below, small tiles while they run in
+//    one round (E = 8, d = 4096, f = 14336: r = 4 (345, 130), 75 (381, 280), 112
+//    (394, 491); one token of E = 64, d = 2048: (42, 18)).
+enum : int { SMALL_WIDE = 0, SMALL_NARROW = 1, SMALL_SLIM = 2 };
+inline int64_t est_rows(int64_t S, int E, int BM) {   // tile rows of BM
+    const int64_t act = S < E ? S : E, full = (S + act * BM / 3) / BM;
+    return act > full ? act : full;
+}
+// first GEMM and dh GEMM: N = f, K = d
+inline SmallTile small_wide_n(int64_t S, int E, int ncols, int wide_cols) {
+    const int64_t r = S / E;
+    const int rows = r <= 40 ? 64 : r <= 112 ? 128 : 0;
+    if (!rows) return {0, 0};
+    return {rows, est_rows(S, E, rows) * cdiv(ncols, wide_cols) >= 192 ? SMALL_WIDE : SMALL_NARROW};
+}
+inline int small_level(int64_t mt, int ncols) {
+    return mt * cdiv(ncols, 64) <= 256 ? SMALL_SLIM : mt * cdiv(ncols, 128) <= 256 ? SMALL_NARROW : SMALL_WIDE;
+}
+// second GEMM from the h buffer, and dX GEMM: N = d
+inline SmallTile small_long_k(int64_t S, int E, int ncols) {
+    const int64_t r = S / E;
+    const bool few = r <= 256 && est_rows(S, E, RS::BM) * cdiv(ncols, RS::BN) <= 128;
+    const int rows = r <= 40 ? 64 : r <= 112 || few ? 128 : 0;
+    if (!rows) return {0, 0};
+    return {rows, small_level(est_rows(S, E, rows), ncols)};
+}
+// second GEMM with h formed on load
+inline SmallTile small_form_h(int64_t S, int E, int ncols) {
+    if (est_rows(S, E, RHW::BM) * cdiv(ncols, RHW::BN) > 96) return {0, 0};
+    const int rows = S / E <= 24 ? 32 : 64;
+    const int64_t mt = est_rows(S, E, rows);
+    if (mt * cdiv(ncols, 256) > 256) return {0, 0};
+    return {rows, small_level(mt, ncols)};
+}
+
 // Raise the dynamic LDS limit of the GEMM kernels once per process.
 hipError_t set_lds_limits() {
     static hipError_t status = [] {
@@ -1044,14 +930,21 @@ hipError_t ffn_fwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
     using C2H = RHW;
     // h buffered between the GEMMs, or (h_on_load) formed again from A, B
     bf16_t* H = a.h_on_load ? nullptr : static_cast<bf16_t*>(a.ws);
-    hipLaunchKernelGGL(g1_kernel<ACT>, dim3(slot_grid(S, a.E, C1::BM, cdiv(a.f, C1::BN))),
-                       dim3(C1::THREADS), C1::LDS, st, (const bf16_t*)a.x, (const bf16_t*)a.w1,
-                       (const bf16_t*)a.w3, a.offsets, a.eti, a.d, a.f, a.E, (bf16_t*)a.A,
-                       (bf16_t*)a.B, H);
-    probe::mark("g1_kernel", st);
+    const SmallTile t1 = small_wide_n(S, a.E, a.f, ACT == ACT_SWIGLU ? 128 : 256);
+    if (t1.rows) {
+        if (hipError_t e = small_first(a, t1, H, st); e != hipSuccess) return e;
+    } else {
+        hipLaunchKernelGGL(g1_kernel<ACT>, dim3(slot_grid(S, a.E, C1::BM, cdiv(a.f, C1::BN))),
+                           dim3(C1::THREADS), C1::LDS, st, (const bf16_t*)a.x,
+                           (const bf16_t*)a.w1, (const bf16_t*)a.w3, a.offsets, a.eti, a.d, a.f,
+                           a.E, (bf16_t*)a.A, (bf16_t*)a.B, H);
+        probe::mark("g1_kernel", st);
+    }
     // the second GEMM over columns [c0, c0 + nc): slot rows into out (ldo
     // apart), or with gs (scatter) added into the token rows of out
     auto second = [&](int c0, int nc, int64_t ldo, bf16_t* out, const float* gs) {
+        const SmallTile t2 = H ? small_long_k(S, a.E, nc) : small_form_h(S, a.E, nc);
+        if (t2.rows) return small_second(a, t2, H, c0, nc, ldo, out, gs, st);
         if (a.h_on_load) {
             auto g2h = gs ? g2h_kernel<ACT, true> : g2h_kernel<ACT, false>;
             hipLaunchKernelGGL(g2h, dim3(slot_grid(S, a.E, C2H::BM, cdiv(nc, C2H::BN))),
@@ -1067,10 +960,10 @@ hipError_t ffn_fwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
                                a.eti, gs);
             probe::mark("g2_kernel", st);
         }
+        return hipGetLastError();
     };
     if (!a.y) {   // O [S, d] for the caller's combine
-        second(0, a.d, (int64_t)a.d, (bf16_t*)a.O, nullptr);
-        return hipGetLastError();
+        return second(0, a.d, (int64_t)a.d, (bf16_t*)a.O, nullptr);
     }
     if (a.scatter) {   // y = 0, then every slot row times its gate added into y
         float* gs = reinterpret_cast<float*>(
@@ -1081,8 +974,7 @@ hipError_t ffn_fwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
         hipLaunchKernelGGL(zero_bf16, grid1d(a.T * a.d / 8, 256), dim3(256), 0, st,
                            static_cast<bf16_t*>(a.y), a.T * a.d);
         probe::mark("zero_bf16", st);
-        second(0, a.d, (int64_t)a.d, static_cast<bf16_t*>(a.y), gs);
-        return hipGetLastError();
+        return second(0, a.d, (int64_t)a.d, static_cast<bf16_t*>(a.y), gs);
     }
     // combined: one column strip of O at a time, straight into y
     const int sw = fwd_strip(S, a.E, a.d, a.h_on_load);
@@ -1090,7 +982,7 @@ hipError_t ffn_fwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
         static_cast<char*>(a.ws) + (a.h_on_load ? 0 : align256((size_t)S * a.f * sizeof(bf16_t))));
     for (int c0 = 0; c0 < a.d; c0 += sw) {
         const int nc = min(sw, a.d - c0);
-        second(c0, nc, (int64_t)nc, strip, nullptr);
+        if (hipError_t e = second(c0, nc, (int64_t)nc, strip, nullptr); e != hipSuccess) return e;
         if (hipError_t e = combine_cols(strip, nc, a.gates, a.tim, a.T, nc, a.k, false, false,
                                         static_cast<bf16_t*>(a.y) + c0, a.d, st);
             e != hipSuccess)
@@ -1110,6 +1002,8 @@ hipError_t ffn_first_act(const FfnArgs& a, bool f32, hipStream_t st) {
         return hipGetLastError();
     }
     if (hipError_t e = set_lds_limits(); e != hipSuccess) return e;
+    if (const SmallTile t1 = small_wide_n(S, a.E, a.f, ACT == ACT_SWIGLU ? 128 : 256); t1.rows)
+        return small_first(a, t1, nullptr, st);
     using C1 = CFirst<ACT>;
     hipLaunchKernelGGL(g1_kernel<ACT>, dim3(slot_grid(S, a.E, C1::BM, cdiv(a.f, C1::BN))),
                        dim3(C1::THREADS), C1::LDS, st, (const bf16_t*)a.x, (const bf16_t*)a.w1,
@@ -1215,12 +1109,17 @@ hipError_t ffn_bwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
                            a.eti, a.d, a.f, (int)a.accumulate_dw, a.dw2);
         probe::mark("g3h_kernel", st);
     }
-    auto g4 = a.h_on_load ? g4_kernel<ACT, false> : g4_kernel<ACT, true>;
-    hipLaunchKernelGGL(g4, dim3(slot_grid(S, a.E, RS::BM, cdiv(a.f, RS::BN))),
-                       dim3(RS::THREADS), RS::LDS, st, (const bf16_t*)a.dy, (const bf16_t*)a.w2,
-                       a.gates, a.offsets, a.eti, a.slot_src, (const float*)gs, a.d, a.f, a.E,
-                       (bf16_t*)a.A, (bf16_t*)a.B, HG, part);
-    probe::mark("g4_kernel", st);
+    const SmallTile t4 = small_wide_n(S, a.E, a.f, 256);
+    if (t4.rows) {
+        if (hipError_t e = small_dact(a, t4, gs, HG, part, nparts, st); e != hipSuccess) return e;
+    } else {
+        auto g4 = a.h_on_load ? g4_kernel<ACT, false> : g4_kernel<ACT, true>;
+        hipLaunchKernelGGL(g4, dim3(slot_grid(S, a.E, RS::BM, cdiv(a.f, RS::BN))),
+                           dim3(RS::THREADS), RS::LDS, st, (const bf16_t*)a.dy,
+                           (const bf16_t*)a.w2, a.gates, a.offsets, a.eti, a.slot_src,
+                           (const float*)gs, a.d, a.f, a.E, (bf16_t*)a.A, (bf16_t*)a.B, HG, part);
+        probe::mark("g4_kernel", st);
+    }
     hipLaunchKernelGGL(dgate_reduce, grid1d(S, 256), dim3(256), 0, st, part, nparts, a.slot_src,
                        a.offsets, a.E, S, a.dgates);
     probe::mark("dgate_reduce", st);
@@ -1236,6 +1135,8 @@ hipError_t ffn_bwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
                        a.dw1, a.dw3);
     probe::mark("g5_kernel", st);
     const int kslices = (GATED ? 2 : 1) * a.f / rs::KS;
+    auto t6 = [&](int nc) { return small_long_k(S, a.E, nc); };
+    if (!a.y && t6(a.d).rows) return small_dx(a, t6(a.d), 0, a.d, (int64_t)a.d, a.dX, false, st);
     if (!a.y) {   // dX_slot [S, d] for the caller's combine
         hipLaunchKernelGGL(g6_kernel<false>, dim3(slot_grid(S, a.E, RS::BM, cdiv(a.d, RS::BN))),
                            dim3(RS::THREADS), RS::LDS, st, (const bf16_t*)a.A, (const bf16_t*)Bx,
@@ -1250,6 +1151,7 @@ hipError_t ffn_bwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
                                static_cast<bf16_t*>(a.y), a.T * a.d);
             probe::mark("zero_bf16", st);
         }
+        if (t6(a.d).rows) return small_dx(a, t6(a.d), 0, a.d, (int64_t)a.d, a.y, true, st);
         hipLaunchKernelGGL(g6_kernel<true>, dim3(slot_grid(S, a.E, RS::BM, cdiv(a.d, RS::BN))),
                            dim3(RS::THREADS), RS::LDS, st, (const bf16_t*)a.A, (const bf16_t*)Bx,
                            (const bf16_t*)a.w1, (const bf16_t*)w3x, a.offsets, a.d, a.f, a.E,
@@ -1262,11 +1164,16 @@ hipError_t ffn_bwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
     const int sw = bwd_strip(S, a.E, a.d);
     for (int c0 = 0; c0 < a.d; c0 += sw) {
         const int nc = min(sw, a.d - c0);
-        hipLaunchKernelGGL(g6_kernel<false>, dim3(slot_grid(S, a.E, RS::BM, cdiv(nc, RS::BN))),
-                           dim3(RS::THREADS), RS::LDS, st, (const bf16_t*)a.A, (const bf16_t*)Bx,
-                           (const bf16_t*)a.w1, (const bf16_t*)w3x, a.offsets, a.d, a.f, a.E,
-                           kslices, c0, nc, (int64_t)nc, strip, a.eti);
-        probe::mark("g6_kernel", st);
+        if (t6(nc).rows) {
+            if (hipError_t e = small_dx(a, t6(nc), c0, nc, (int64_t)nc, strip, false, st); e != hipSuccess)
+                return e;
+        } else {
+            hipLaunchKernelGGL(g6_kernel<false>, dim3(slot_grid(S, a.E, RS::BM, cdiv(nc, RS::BN))),
+                               dim3(RS::THREADS), RS::LDS, st, (const bf16_t*)a.A,
+                               (const bf16_t*)Bx, (const bf16_t*)a.w1, (const bf16_t*)w3x,
+                               a.offsets, a.d, a.f, a.E, kslices, c0, nc, (int64_t)nc, strip, a.eti);
+            probe::mark("g6_kernel", st);
+        }
         if (hipError_t e = combine_cols(strip, nc, nullptr, a.tim, a.T, nc, a.k, false,
                                         a.accumulate, static_cast<bf16_t*>(a.y) + c0, a.d, st);
             e != hipSuccess)

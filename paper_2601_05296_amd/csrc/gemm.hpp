@@ -235,34 +235,50 @@ struct SlotTile {
 template <int THREADS>
 __device__ bool find_slot_tile(int* sh, const int32_t* __restrict__ offsets, int E, int BM, int NT,
                                int bid, int BN, SlotTile& t, int GM = 0) {
-    static_assert(THREADS >= 256, "one thread per expert");
+    constexpr int EPT = THREADS >= 256 ? 1 : 256 / THREADS;   // consecutive experts per thread
+    constexpr int NWS = 256 / EPT / WAVE;                     // waves that hold experts
+    static_assert(THREADS % WAVE == 0 && NWS <= 4, "at most 256 experts");
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
-    int tiles = 0, cnt = 0, off = 0;
-    if (tid < E) {
-        off = offsets[tid];
-        cnt = offsets[tid + 1] - off;
-        tiles = ((cnt + BM - 1) / BM) * NT;
+    int tiles[EPT], cnt[EPT], off[EPT], sum = 0;
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) {
+        const int x = tid * EPT + u;
+        off[u] = cnt[u] = 0;
+        if (x < E) {
+            off[u] = offsets[x];
+            cnt[u] = offsets[x + 1] - off[u];
+        }
+        tiles[u] = ((cnt[u] + BM - 1) / BM) * NT;
+        sum += tiles[u];
     }
     // expert e's tiles are [start, end): a wave-level scan, plus the totals of
-    // the waves before (E <= 256: four waves)
-    const int inc = wave_incl_scan(tiles);
-    if (wv < 4 && lane == WAVE - 1) sh[wv] = inc;
+    // the waves before
+    const int inc = wave_incl_scan(sum);
+    if (wv < NWS && lane == WAVE - 1) sh[wv] = inc;
     __syncthreads();
-    const int total = sh[0] + sh[1] + sh[2] + sh[3];
+    int total = 0, start = inc - sum;
+#pragma unroll
+    for (int w = 0; w < NWS; ++w) {
+        total += sh[w];
+        start += w < wv ? sh[w] : 0;
+    }
     if (bid >= total) return false;
     bid = xcd_remap(bid, total);
-    if (tid < E) {
-        int end = inc;
-        for (int w = 0; w < wv; ++w) end += sh[w];
-        const int start = end - tiles;
-        if (bid >= start && bid < end) { sh[4] = tid; sh[5] = bid - start; sh[6] = off; sh[7] = cnt; }
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) {
+        if (bid >= start && bid < start + tiles[u]) {
+            sh[4] = tid * EPT + u;
+            sh[5] = bid - start;
+            sh[6] = off[u];
+            sh[7] = cnt[u];
+        }
+        start += tiles[u];
     }
     __syncthreads();
     const int e = sh[4], local = sh[5];
-    off = sh[6];
-    cnt = sh[7];
+    const int eoff = sh[6], ecnt = sh[7];
     __syncthreads();
-    const int nmt = (cnt + BM - 1) / BM;
+    const int nmt = (ecnt + BM - 1) / BM;
     const int gm = GM > 0 ? GM : nmt;         // M tiles per group
     const int full = nmt / gm * gm;           // M tiles in whole groups
     int mt, nt;
@@ -276,9 +292,9 @@ __device__ bool find_slot_tile(int* sh, const int32_t* __restrict__ offsets, int
         nt = l2 / rem;
     }
     t.e = e;
-    t.off = off;
+    t.off = eoff;
     t.m0 = mt * BM;
-    t.mrows = min(BM, cnt - t.m0);
+    t.mrows = min(BM, ecnt - t.m0);
     t.n0 = nt * BN;
     return true;
 }

@@ -96,10 +96,17 @@ struct Cfg {
 
 // ---- LDS layouts -------------------------------------------------------------------
 __device__ __forceinline__ int kc_off(int r, int c) { return r * 128 + ((c ^ ((r >> 1) & 7)) << 4); }
+// MC swizzle of k row k, XOR-ed into its 32-byte chunk index. 64-column rows
+// (4 chunks, two rows to the 256 bytes of the banks): k rows 0, 1 of a read
+// already differ by half the banks, rows 2, 3 take the other chunk pair.
+template <int R>
+__device__ __forceinline__ int mc_swz(int k) {
+    static_assert(R >= 64, "the MC swizzle permutes 32-byte chunks of a k row");
+    return R == 64 ? (k & 2) : ((k & 3) << 1);
+}
 template <int R>
 __device__ __forceinline__ int mc_off(int k, int p) {   // p: logical 16-byte chunk of k row
-    static_assert(R >= 128, "the MC swizzle permutes 32-byte chunks 0..7 of a k row");
-    return k * (R * 2) + ((((p >> 1) ^ ((k & 3) << 1)) << 5) | ((p & 1) << 4));
+    return k * (R * 2) + ((((p >> 1) ^ mc_swz<R>(k)) << 5) | ((p & 1) << 4));
 }
 
 // ---- fragment reads (32 rows x 16 k of MFMA step kk of the slice) ------------------
@@ -116,8 +123,8 @@ __device__ __forceinline__ bf16x8 frag_mc(const char* tile, int rbase, int kk, i
     const int cc = (rbase >> 4) + (g & 1);
     const int cb = (p & 3) * 8;
     typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
-    const char* a0 = tile + k * (R * 2) + (((cc ^ ((k & 3) << 1)) << 5) | cb);
-    const char* a1 = tile + (k + 4) * (R * 2) + (((cc ^ (((k + 4) & 3) << 1)) << 5) | cb);
+    const char* a0 = tile + k * (R * 2) + (((cc ^ mc_swz<R>(k)) << 5) | cb);
+    const char* a1 = tile + (k + 4) * (R * 2) + (((cc ^ mc_swz<R>(k + 4)) << 5) | cb);
     const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(a0));
     const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(a1));
     typedef short i16x8 __attribute__((ext_vector_type(8)));

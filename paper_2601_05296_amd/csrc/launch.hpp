@@ -66,4 +66,18 @@ size_t ffn_bwd_workspace(int64_t T, int d, int f, int E, int k, bool f32, bool c
                          bool h_on_load, bool scatter);
 hipError_t ffn_bwd(const FfnArgs& a, bool f32, hipStream_t st);
 
+// ---- row-wise GEMMs for few rows per expert (ffn_small.hip) ----
+// rows per tile (32, 64 or 128; 0: not these kernels) and column level (0 wide,
+// 1 narrow, 2 slim)
+struct SmallTile { int rows, level; };
+hipError_t small_first(const FfnArgs& a, SmallTile v, void* H, hipStream_t st);
+// columns [c0, c0 + nc) of the second GEMM from H, or (H null; 32 or 64 rows)
+// from h formed of A and B; gs: added into the token rows of out
+hipError_t small_second(const FfnArgs& a, SmallTile v, const void* H, int c0, int nc, int64_t ldo,
+                        void* out, const float* gs, hipStream_t st);
+hipError_t small_dact(const FfnArgs& a, SmallTile v, const float* gs, void* HG, float* part, int nparts,
+                      hipStream_t st);
+hipError_t small_dx(const FfnArgs& a, SmallTile v, int c0, int nc, int64_t ldo, void* out, bool scatter,
+                    hipStream_t st);
+
 }  // namespace moe

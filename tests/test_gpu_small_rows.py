@@ -1,0 +1,111 @@
+"""The row-wise GEMMs for few rows per expert return the bits of the 256-row
+kernels: the same tokens, once alone (few rows per expert) and once repeated so
+often that the 256-row kernels run, give equal A, B, O, dA, dB, dX_slot,
+d_gates, y and dx. Expert loads sit on the edges of the 32-, 64- and 128-row
+tiles; d and f are odd multiples of 64 (half-empty column tiles)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2601_05296_amd import binding as B
+from tests.parity import dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _bf16(rng, shape, std):
+    t = torch.from_numpy(rng.standard_normal(size=shape, dtype=np.float32) * np.float32(std))
+    return t.to(torch.bfloat16).cuda()
+
+
+def _ffn(ids, gates, x, dy, w, act, h_on_load, atomic):
+    """Forward and backward of the FFN calls on ids [T, 1]; slot order is
+    expert by expert, ascending token."""
+    w1, w3, w2 = w
+    T, k = ids.shape
+    E, d, f = w1.shape
+    ix = oracle.build_index(ids, E)
+    offsets, eti, tim, ss = (dev(a) for a in (ix.offsets, ix.eti, ix.tim, ix.slot_src))
+    S = T * k
+    gated = act == "swiglu"
+    flags = B.ACT_FLAG[act] | (B.MOE_H_ON_LOAD if h_on_load else 0)
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    f32 = dict(dtype=torch.float32, device="cuda")
+    A = torch.empty((S, f), **bf)
+    Bm = torch.empty((S, f), **bf) if gated else None
+    dw1, dw2 = torch.empty((E, d, f), **f32), torch.empty((E, f, d), **f32)
+    dw3 = torch.empty((E, d, f), **f32) if gated else None
+    dg = torch.empty((T, k), **f32)
+    w3g = w3 if gated else None
+
+    def ws(n):
+        return torch.empty(max(n, 16), dtype=torch.uint8, device="cuda")
+
+    out = {}
+    if atomic:
+        cf = flags | B.MOE_ATOMIC_COMBINE
+        y, dx = torch.empty((T, d), **bf), torch.empty((T, d), **bf)
+        n = B.moe_ffn_fwd_combine_workspace_size(T, d, f, E, k, cf)
+        B.moe_ffn_fwd_combine(x, w1, w3g, w2, offsets, eti, gates, tim, T, d, f, E, k, cf, A, Bm,
+                              y, ws(n), n)
+        out.update(A=A.clone(), y=y)
+        n = B.moe_ffn_bwd_combine_workspace_size(T, d, f, E, k, cf)
+        B.moe_ffn_bwd_combine(dy, x, w1, w3g, w2, gates, offsets, eti, ss, tim, A, Bm, T, d, f, E,
+                              k, cf, dw1, dw3, dw2, dg, dx, ws(n), n)
+        out.update(dx=dx)
+        rows = {"A": 1, "dA": 1}
+    else:
+        O, dX = torch.empty((S, d), **bf), torch.empty((S, d), **bf)
+        n = B.moe_ffn_fwd_workspace_size(T, d, f, E, k, flags)
+        B.moe_ffn_fwd(x, w1, w3g, w2, offsets, eti, T, d, f, E, k, flags, A, Bm, O, ws(n), n)
+        out.update(A=A.clone(), O=O)
+        if gated:
+            out["B"] = Bm.clone()
+        n = B.moe_ffn_bwd_workspace_size(T, d, f, E, k, flags)
+        B.moe_ffn_bwd(dy, x, w1, w3g, w2, gates, offsets, eti, ss, A, Bm, T, d, f, E, k, flags,
+                      dw1, dw3, dw2, dg, dX, ws(n), n)
+        out.update(dX=dX)
+        if gated:
+            out["dB"] = Bm
+    out.update(dA=A, dg=dg)
+    torch.cuda.synchronize()
+    # slot-ordered arrays back to token order
+    order = torch.from_numpy(ix.tim[:, 0].astype(np.int64)).cuda()
+    return {n: t if n in ("y", "dx", "dg") else t[order] for n, t in out.items()}
+
+
+EDGES_64 = [1, 31, 32, 33, 63, 64, 65, 0]              # mean 36: 64-row tiles
+EDGES_128 = [97, 127, 128, 129, 1, 64, 65, 100]        # mean 88: 128-row tiles
+
+
+@pytest.mark.parametrize("counts,d,f,act,h_on_load,atomic", [
+    ([3, 0, 0, 1, 0, 0, 2, 0], 192, 320, "swiglu", True, False),     # a few rows, slim tiles
+    (EDGES_64, 192, 320, "swiglu", True, False),
+    (EDGES_64, 320, 192, "swiglu", False, True),
+    (EDGES_64, 128, 704, "relu", True, True),
+    (EDGES_128, 192, 320, "swiglu", False, False),
+    (EDGES_128, 320, 448, "silu", True, True),
+    # enough experts for the wide tiles, forward and backward
+    (EDGES_64 * 8, 192, 320, "swiglu", True, False),
+    (EDGES_64 * 24, 576, 576, "silu", False, True),
+    (EDGES_128 * 12, 576, 576, "swiglu", False, False),
+    (EDGES_128 * 12, 64, 64, "swiglu", True, True)])
+def test_small_rows_same_bits(counts, d, f, act, h_on_load, atomic):
+    E, T = len(counts), sum(counts)
+    rng = np.random.Generator(np.random.PCG64(T + d + f))
+    ids = rng.permutation(np.repeat(np.arange(E), counts)).astype(np.int32)[:, None]
+    x, dy = _bf16(rng, (T, d), 1.0), _bf16(rng, (T, d), 1.0)
+    w = (_bf16(rng, (E, d, f), d ** -0.5), _bf16(rng, (E, d, f), d ** -0.5),
+         _bf16(rng, (E, f, d), f ** -0.5))
+    gates = torch.from_numpy(rng.random((T, 1), dtype=np.float32)).cuda()
+    one = _ffn(ids, gates, x, dy, w, act, h_on_load, atomic)
+    # repeats for a mean of 300 rows per expert and 100 row tiles of 128, beyond
+    # every rule of the small kernels
+    n = -(-max(300 * E, 100 * 128) // T)
+    rep = _ffn(np.tile(ids, (n, 1)), gates.repeat(n, 1), x.repeat(n, 1), dy.repeat(n, 1), w, act,
+               h_on_load, atomic)
+    for name, a in one.items():
+        assert torch.isfinite(a.float()).all(), name
+        assert torch.equal(a, rep[name][:T]), name
+        assert torch.equal(a, rep[name][-T:]), name
