@@ -36,7 +36,7 @@
 // waits for the host. The weight-gradient GEMMs (G3, G5) have a fixed tile grid
 // per expert and loop over the expert's slots as K.
 //
-// The float32 debug mode uses plain one-output-per-thread kernels.
+// The float32 mode is in ffn_f32.hip.
 #include "common.hpp"
 #include "ffn_epi.hpp"
 #include "gemm.hpp"
@@ -630,149 +630,6 @@ __global__ void dgate_reduce(const float* __restrict__ part, int nparts,
     dgates[slot_src[s]] = acc;
 }
 
-// ============================ float32 debug kernels ===============================
-
-__device__ int expert_of(const int32_t* offsets, int E, int64_t s) {
-    int lo = 0, hi = E - 1;  // largest e with offsets[e] <= s
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (offsets[mid] <= s) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-__device__ float silu32(float a) { return a / (1.0f + __expf(-a)); }
-
-// h and its derivatives from the first-layer outputs (b unused when non-gated)
-template <int ACT>
-__device__ float f32_h(float a, float b) {
-    if constexpr (ACT == ACT_SWIGLU) return silu32(a) * b;
-    else if constexpr (ACT == ACT_RELU) return a > 0.f ? a : 0.f;
-    else return silu32(a);
-}
-
-template <int ACT>
-__global__ void f32_g1(const float* x, const float* w1, const float* w3, const int32_t* offsets,
-                       const int32_t* eti, int64_t S, int d, int f, int E, float* A, float* B) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= S * f) return;
-    const int64_t s = id / f;
-    const int n = (int)(id % f);
-    if (s >= offsets[E]) return;
-    const int e = expert_of(offsets, E, s);
-    const float* xr = x + (int64_t)eti[s] * d;
-    float a = 0.f, b = 0.f;
-    for (int i = 0; i < d; ++i) {
-        a = fmaf(xr[i], w1[((int64_t)e * d + i) * f + n], a);
-        if constexpr (ACT == ACT_SWIGLU) b = fmaf(xr[i], w3[((int64_t)e * d + i) * f + n], b);
-    }
-    A[id] = a;
-    if constexpr (ACT == ACT_SWIGLU) B[id] = b;
-}
-
-template <int ACT>
-__global__ void f32_g2(const float* A, const float* B, const float* w2, const int32_t* offsets,
-                       int64_t S, int d, int f, int E, float* O) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= S * d) return;
-    const int64_t s = id / d;
-    const int n = (int)(id % d);
-    const int e = expert_of(offsets, E, s);
-    float o = 0.f;
-    for (int c = 0; c < f; ++c)
-        o = fmaf(f32_h<ACT>(A[s * f + c], ACT == ACT_SWIGLU ? B[s * f + c] : 0.f),
-                 w2[((int64_t)e * f + c) * d + n], o);
-    O[id] = o;
-}
-
-template <int ACT>
-__global__ void f32_g3(const float* A, const float* B, const float* dy, const float* gates,
-                       const int32_t* offsets, const int32_t* eti, const int32_t* slot_src,
-                       int d, int f, int E, int add, float* dw2) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= (int64_t)E * f * d) return;
-    const int e = (int)(id / ((int64_t)f * d));
-    const int c = (int)((id / d) % f);
-    const int n = (int)(id % d);
-    float acc = 0.f;
-    for (int s = offsets[e]; s < offsets[e + 1]; ++s) {
-        const float h = f32_h<ACT>(A[(int64_t)s * f + c],
-                                   ACT == ACT_SWIGLU ? B[(int64_t)s * f + c] : 0.f);
-        acc = fmaf(gates[slot_src[s]] * h, dy[(int64_t)eti[s] * d + n], acc);
-    }
-    dw2[id] = add ? dw2[id] + acc : acc;
-}
-
-// one thread per slot: u, d_gate, dA, dB (in place)
-template <int ACT>
-__global__ void f32_g4(const float* dy, const float* w2, const float* gates,
-                       const int32_t* offsets, const int32_t* eti, const int32_t* slot_src,
-                       int64_t S, int d, int f, int E, float* A, float* B, float* dgates) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S || s >= offsets[E]) return;
-    const int e = expert_of(offsets, E, s);
-    const float* dyr = dy + (int64_t)eti[s] * d;
-    const float g = gates[slot_src[s]];
-    float dg = 0.f;
-    for (int c = 0; c < f; ++c) {
-        float u = 0.f;
-        const float* wr = w2 + ((int64_t)e * f + c) * d;
-        for (int n = 0; n < d; ++n) u = fmaf(dyr[n], wr[n], u);
-        const float a = A[s * f + c];
-        const float dh = g * u;
-        if constexpr (ACT == ACT_SWIGLU) {
-            const float b = B[s * f + c];
-            const float sg = 1.0f / (1.0f + __expf(-a));
-            dg = fmaf(u, a * sg * b, dg);
-            A[s * f + c] = dh * b * sg * (1.0f + a * (1.0f - sg));
-            B[s * f + c] = dh * a * sg;
-        } else if constexpr (ACT == ACT_RELU) {
-            dg = fmaf(u, a > 0.f ? a : 0.f, dg);
-            A[s * f + c] = a > 0.f ? dh : 0.f;
-        } else {
-            const float sg = 1.0f / (1.0f + __expf(-a));
-            dg = fmaf(u, a * sg, dg);
-            A[s * f + c] = dh * sg * (1.0f + a * (1.0f - sg));
-        }
-    }
-    dgates[slot_src[s]] = dg;
-}
-
-template <int ACT>
-__global__ void f32_g5(const float* x, const float* dA, const float* dB, const int32_t* offsets,
-                       const int32_t* eti, int d, int f, int E, int add, float* dw1, float* dw3) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= (int64_t)E * d * f) return;
-    const int e = (int)(id / ((int64_t)d * f));
-    const int i = (int)((id / f) % d);
-    const int c = (int)(id % f);
-    float a1 = 0.f, a3 = 0.f;
-    for (int s = offsets[e]; s < offsets[e + 1]; ++s) {
-        const float xv = x[(int64_t)eti[s] * d + i];
-        a1 = fmaf(xv, dA[(int64_t)s * f + c], a1);
-        if constexpr (ACT == ACT_SWIGLU) a3 = fmaf(xv, dB[(int64_t)s * f + c], a3);
-    }
-    dw1[id] = add ? dw1[id] + a1 : a1;
-    if constexpr (ACT == ACT_SWIGLU) dw3[id] = add ? dw3[id] + a3 : a3;
-}
-
-template <int ACT>
-__global__ void f32_g6(const float* dA, const float* dB, const float* w1, const float* w3,
-                       const int32_t* offsets, int64_t S, int d, int f, int E, float* dX) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= S * d) return;
-    const int64_t s = id / d;
-    const int i = (int)(id % d);
-    const int e = expert_of(offsets, E, s);
-    const float* r1 = w1 + ((int64_t)e * d + i) * f;
-    const float* r3 = w3 + ((int64_t)e * d + i) * f;
-    float acc = 0.f;
-    for (int c = 0; c < f; ++c) {
-        acc = fmaf(dA[s * f + c], r1[c], acc);
-        if constexpr (ACT == ACT_SWIGLU) acc = fmaf(dB[s * f + c], r3[c], acc);
-    }
-    dX[id] = acc;
-}
-
 inline dim3 grid1d(int64_t n, int bs) { return dim3((unsigned)((n + bs - 1) / bs)); }
 
 // number of workgroups for a row-wise grouped GEMM (upper bound on tiles)
@@ -897,6 +754,14 @@ inline int bwd_strip(int64_t S, int E, int d) { return strip_width(S, E, d, RS::
 
 }  // namespace
 
+hipError_t dgate_sum(const float* part, int nparts, const int32_t* slot_src,
+                     const int32_t* offsets, int E, int64_t S, float* dgates, hipStream_t st) {
+    hipLaunchKernelGGL(dgate_reduce, grid1d(S, 256), dim3(256), 0, st, part, nparts, slot_src,
+                       offsets, E, S, dgates);
+    probe::mark("dgate_reduce", st);
+    return hipGetLastError();
+}
+
 size_t ffn_fwd_workspace(int64_t T, int d, int f, int E, int k, bool f32, bool combined,
                          bool h_on_load, bool scatter) {
     const size_t S = (size_t)T * k;
@@ -910,21 +775,8 @@ size_t ffn_fwd_workspace(int64_t T, int d, int f, int E, int k, bool f32, bool c
 namespace {
 
 template <int ACT>
-hipError_t ffn_fwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
+hipError_t ffn_fwd_act(const FfnArgs& a, hipStream_t st) {
     const int64_t S = a.T * a.k;
-    if (f32) {
-        hipLaunchKernelGGL(f32_g1<ACT>, grid1d(S * a.f, 256), dim3(256), 0, st,
-                           (const float*)a.x, (const float*)a.w1, (const float*)a.w3, a.offsets,
-                           a.eti, S, a.d, a.f, a.E, (float*)a.A, (float*)a.B);
-        probe::mark("f32_g1", st);
-        float* O = a.y ? static_cast<float*>(a.ws) : (float*)a.O;
-        hipLaunchKernelGGL(f32_g2<ACT>, grid1d(S * a.d, 256), dim3(256), 0, st,
-                           (const float*)a.A, (const float*)a.B, (const float*)a.w2, a.offsets, S,
-                           a.d, a.f, a.E, O);
-        probe::mark("f32_g2", st);
-        if (a.y) return combine(O, a.gates, a.tim, a.T, a.d, a.k, true, false, a.y, st);
-        return hipGetLastError();
-    }
     if (hipError_t e = set_lds_limits(); e != hipSuccess) return e;
     using C1 = CFirst<ACT>;
     using C2H = RHW;
@@ -992,15 +844,8 @@ hipError_t ffn_fwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
 }
 
 template <int ACT>
-hipError_t ffn_first_act(const FfnArgs& a, bool f32, hipStream_t st) {
+hipError_t ffn_first_act(const FfnArgs& a, hipStream_t st) {
     const int64_t S = a.T * a.k;
-    if (f32) {
-        hipLaunchKernelGGL(f32_g1<ACT>, grid1d(S * a.f, 256), dim3(256), 0, st,
-                           (const float*)a.x, (const float*)a.w1, (const float*)a.w3, a.offsets,
-                           a.eti, S, a.d, a.f, a.E, (float*)a.A, (float*)a.B);
-        probe::mark("f32_g1", st);
-        return hipGetLastError();
-    }
     if (hipError_t e = set_lds_limits(); e != hipSuccess) return e;
     if (const SmallTile t1 = small_wide_n(S, a.E, a.f, ACT == ACT_SWIGLU ? 128 : 256); t1.rows)
         return small_first(a, t1, nullptr, st);
@@ -1016,18 +861,20 @@ hipError_t ffn_first_act(const FfnArgs& a, bool f32, hipStream_t st) {
 }  // namespace
 
 hipError_t ffn_first(const FfnArgs& a, bool f32, hipStream_t st) {
+    if (f32) return f32_first(a, st);
     switch (a.act) {
-    case ACT_SILU: return ffn_first_act<ACT_SILU>(a, f32, st);
-    case ACT_RELU: return ffn_first_act<ACT_RELU>(a, f32, st);
-    default: return ffn_first_act<ACT_SWIGLU>(a, f32, st);
+    case ACT_SILU: return ffn_first_act<ACT_SILU>(a, st);
+    case ACT_RELU: return ffn_first_act<ACT_RELU>(a, st);
+    default: return ffn_first_act<ACT_SWIGLU>(a, st);
     }
 }
 
 hipError_t ffn_fwd(const FfnArgs& a, bool f32, hipStream_t st) {
+    if (f32) return f32_fwd(a, st);
     switch (a.act) {
-    case ACT_SILU: return ffn_fwd_act<ACT_SILU>(a, f32, st);
-    case ACT_RELU: return ffn_fwd_act<ACT_RELU>(a, f32, st);
-    default: return ffn_fwd_act<ACT_SWIGLU>(a, f32, st);
+    case ACT_SILU: return ffn_fwd_act<ACT_SILU>(a, st);
+    case ACT_RELU: return ffn_fwd_act<ACT_RELU>(a, st);
+    default: return ffn_fwd_act<ACT_SWIGLU>(a, st);
     }
 }
 
@@ -1055,30 +902,9 @@ size_t ffn_bwd_workspace(int64_t T, int d, int f, int E, int k, bool f32, bool c
 namespace {
 
 template <int ACT>
-hipError_t ffn_bwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
+hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
     const int64_t S = a.T * a.k;
     constexpr bool GATED = ACT == ACT_SWIGLU;
-    if (f32) {
-        hipLaunchKernelGGL(f32_g3<ACT>, grid1d((int64_t)a.E * a.f * a.d, 256), dim3(256), 0, st,
-                           (const float*)a.A, (const float*)a.B, (const float*)a.dy, a.gates,
-                           a.offsets, a.eti, a.slot_src, a.d, a.f, a.E, (int)a.accumulate_dw, a.dw2);
-        probe::mark("f32_g3", st);
-        hipLaunchKernelGGL(f32_g4<ACT>, grid1d(S, 64), dim3(64), 0, st, (const float*)a.dy,
-                           (const float*)a.w2, a.gates, a.offsets, a.eti, a.slot_src, S, a.d, a.f,
-                           a.E, (float*)a.A, (float*)a.B, a.dgates);
-        probe::mark("f32_g4", st);
-        hipLaunchKernelGGL(f32_g5<ACT>, grid1d((int64_t)a.E * a.d * a.f, 256), dim3(256), 0, st,
-                           (const float*)a.x, (const float*)a.A, (const float*)a.B, a.offsets,
-                           a.eti, a.d, a.f, a.E, (int)a.accumulate_dw, a.dw1, a.dw3);
-        probe::mark("f32_g5", st);
-        float* dX = a.y ? static_cast<float*>(a.ws) : (float*)a.dX;
-        hipLaunchKernelGGL(f32_g6<ACT>, grid1d(S * a.d, 256), dim3(256), 0, st, (const float*)a.A,
-                           (const float*)a.B, (const float*)a.w1, (const float*)a.w3, a.offsets,
-                           S, a.d, a.f, a.E, dX);
-        probe::mark("f32_g6", st);
-        if (a.y) return combine(dX, nullptr, a.tim, a.T, a.d, a.k, true, a.accumulate, a.y, st);
-        return hipGetLastError();
-    }
     if (hipError_t e = set_lds_limits(); e != hipSuccess) return e;
     using C5 = CFirst<ACT>;
     using C3H = RHW;
@@ -1120,9 +946,9 @@ hipError_t ffn_bwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
                            (const float*)gs, a.d, a.f, a.E, (bf16_t*)a.A, (bf16_t*)a.B, HG, part);
         probe::mark("g4_kernel", st);
     }
-    hipLaunchKernelGGL(dgate_reduce, grid1d(S, 256), dim3(256), 0, st, part, nparts, a.slot_src,
-                       a.offsets, a.E, S, a.dgates);
-    probe::mark("dgate_reduce", st);
+    if (hipError_t e = dgate_sum(part, nparts, a.slot_src, a.offsets, a.E, S, a.dgates, st);
+        e != hipSuccess)
+        return e;
     if (!a.h_on_load) {
         hipLaunchKernelGGL(g3_kernel, dim3(wgrad_grid(a.E, cdiv(a.f, RS::BM), cdiv(a.d, RS::BN))),
                            dim3(RS::THREADS), RS::LDS, st, (const bf16_t*)HG, (const bf16_t*)a.dy,
@@ -1185,10 +1011,11 @@ hipError_t ffn_bwd_act(const FfnArgs& a, bool f32, hipStream_t st) {
 }  // namespace
 
 hipError_t ffn_bwd(const FfnArgs& a, bool f32, hipStream_t st) {
+    if (f32) return f32_bwd(a, st);
     switch (a.act) {
-    case ACT_SILU: return ffn_bwd_act<ACT_SILU>(a, f32, st);
-    case ACT_RELU: return ffn_bwd_act<ACT_RELU>(a, f32, st);
-    default: return ffn_bwd_act<ACT_SWIGLU>(a, f32, st);
+    case ACT_SILU: return ffn_bwd_act<ACT_SILU>(a, st);
+    case ACT_RELU: return ffn_bwd_act<ACT_RELU>(a, st);
+    default: return ffn_bwd_act<ACT_SWIGLU>(a, st);
     }
 }
 

@@ -66,6 +66,14 @@ size_t ffn_bwd_workspace(int64_t T, int d, int f, int E, int k, bool f32, bool c
                          bool h_on_load, bool scatter);
 hipError_t ffn_bwd(const FfnArgs& a, bool f32, hipStream_t st);
 
+// d_gates[slot_src[s]] = sum of slot s's nparts partial sums
+hipError_t dgate_sum(const float* part, int nparts, const int32_t* slot_src,
+                     const int32_t* offsets, int E, int64_t S, float* dgates, hipStream_t st);
+// float32 mode (ffn_f32.hip)
+hipError_t f32_first(const FfnArgs& a, hipStream_t st);
+hipError_t f32_fwd(const FfnArgs& a, hipStream_t st);
+hipError_t f32_bwd(const FfnArgs& a, hipStream_t st);
+
 // ---- row-wise GEMMs for few rows per expert (ffn_small.hip) ----
 // rows per tile (32, 64 or 128; 0: not these kernels) and column level (0 wide,
 // 1 narrow, 2 slim)

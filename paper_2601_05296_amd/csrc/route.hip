@@ -12,7 +12,7 @@
 // k rounds of (local best, two cross-lane exchanges), ties going to the lower
 // expert id.
 //
-// f32 path (debug mode): one thread per token, float32 FMA.
+// f32 path: float32 matrix instructions (route_f32).
 #include "common.hpp"
 #include "gemm.hpp"
 #include "launch.hpp"
@@ -224,40 +224,105 @@ route_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg,
     }
 }
 
-__global__ void route_f32(const float* __restrict__ x, const float* __restrict__ wg,
-                          const float* __restrict__ bias, int64_t T, int d, int E, int k,
-                          int renorm, int32_t* __restrict__ ids, float* __restrict__ gates,
-                          float* __restrict__ logits) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    float l[256];
-    float mx = -INFINITY;
-    for (int e = 0; e < E; ++e) {
-        float a = 0.f;
-        for (int i = 0; i < d; ++i) a = fmaf(x[t * d + i], wg[(int64_t)e * d + i], a);
-        if (bias) a += bias[e];
-        l[e] = a;
-        if (logits) logits[t * E + e] = a;
-        mx = fmaxf(mx, a);
+// f32: 16 tokens per workgroup. The product runs on v_mfma_f32_16x16x4_f32
+// straight from global memory, each of the four waves taking a quarter of K for
+// all experts; the partial logits meet in LDS, and 16 lanes per token then take
+// softmax and top-k. A lane loads 4 consecutive k (16 bytes) and feeds them to
+// four MFMAs, so the k of MFMA j, lane group g are 16q + 4g + j on both operands.
+// Few tokens and a short K: latency is the bound (T = 1024, d = 256, E = 8: 172
+// us with one thread per token and serial dot products).
+constexpr int RF_TOK = 16;
+constexpr int RF_THREADS = 256;
+
+template <int NE>   // 16-expert fragments, E <= 16 * NE
+__global__ void __launch_bounds__(RF_THREADS)
+route_f32(const float* __restrict__ x, const float* __restrict__ wg,
+          const float* __restrict__ bias, int64_t T, int d, int E, int k, int renorm,
+          int32_t* __restrict__ ids, float* __restrict__ gates, float* __restrict__ logits) {
+    constexpr int EP = NE * 16;
+    __shared__ float part[4][RF_TOK][EP];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int col = lane & 15, grp = lane >> 4;
+    const int64_t t0 = (int64_t)blockIdx.x * RF_TOK;
+    {
+        f32x4 acc[NE];
+#pragma unroll
+        for (int i = 0; i < NE; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int kq = d / 4;   // this wave's share of K (a multiple of 16)
+        const int64_t k0 = (int64_t)wv * kq + grp * 4;
+        const int64_t tr = t0 + col < T ? t0 + col : T - 1;
+        const float* xr = x + tr * d + k0;
+        for (int q = 0; q < kq; q += 16) {
+            const f32x4 a = *reinterpret_cast<const f32x4*>(xr + q);
+#pragma unroll
+            for (int fe = 0; fe < NE; ++fe) {
+                const int e = min(fe * 16 + col, E - 1);
+                const f32x4 w = *reinterpret_cast<const f32x4*>(wg + (int64_t)e * d + k0 + q);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[fe] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j], a[j], acc[fe], 0, 0, 0);
+            }
+        }
+        // lane holds token col, experts fe * 16 + 4 * grp + r
+#pragma unroll
+        for (int fe = 0; fe < NE; ++fe)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[wv][col][fe * 16 + grp * 4 + r] = acc[fe][r];
     }
+    __syncthreads();
+    // 16 lanes per token: lane j takes experts j, j + 16, ...
+    const int tok = threadIdx.x >> 4, j16 = threadIdx.x & 15;
+    const int64_t t = t0 + tok;
+    float* l = part[0][tok];
+    float mx = -INFINITY;
+    for (int e = j16; e < E; e += 16) {
+        float v = (l[e] + part[1][tok][e]) + (part[2][tok][e] + part[3][tok][e]);
+        if (bias) v += bias[e];
+        l[e] = v;
+        if (logits && t < T) logits[t * E + e] = v;
+        mx = fmaxf(mx, v);
+    }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
     float z = 0.f;
-    for (int e = 0; e < E; ++e) z += __expf(l[e] - mx);
-    unsigned long long taken[4] = {0ull, 0ull, 0ull, 0ull};
+    for (int e = j16; e < E; e += 16) z += __expf(l[e] - mx);
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) z += __shfl_xor(z, o, 64);
+    // k rounds over the experts not taken yet: the largest logit, ties to the
+    // lower id. A NaN is never larger than a number; where the lowest free
+    // expert's logit is NaN, no number is larger than it either, and it is taken.
+    unsigned taken = 0;   // bit i: expert j16 + 16 * i
     float pe[16];
+    int be_[16];
     float ssum = 0.f;
     for (int j = 0; j < k; ++j) {
-        int be = -1;
-        float bv = 0.f;
-        for (int e = 0; e < E; ++e) {
-            if ((taken[e >> 6] >> (e & 63)) & 1ull) continue;
-            if (be < 0 || l[e] > bv) { be = e; bv = l[e]; }
+        float bv = -INFINITY;
+        int be = E, first = E, nan = 0;
+        for (int i = 0, e = j16; e < E; ++i, e += 16) {
+            if ((taken >> i) & 1u) continue;
+            const float v = l[e];
+            if (first == E) { first = e; nan = v != v; }
+            if (v > bv || (v == bv && e < be)) { bv = v; be = e; }
         }
-        taken[be >> 6] |= 1ull << (be & 63);
-        ids[t * k + j] = be;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            const float ov = __shfl_xor(bv, o, 64);
+            const int oe = __shfl_xor(be, o, 64), of = __shfl_xor(first, o, 64);
+            const int on = __shfl_xor(nan, o, 64);
+            if (ov > bv || (ov == bv && oe < be)) { bv = ov; be = oe; }
+            if (of < first) { first = of; nan = on; }
+        }
+        if (nan) { be = first; bv = __builtin_nanf(""); }
+        if ((be & 15) == j16) taken |= 1u << (be >> 4);
+        be_[j] = be;
         pe[j] = __expf(bv - mx);
         ssum += pe[j];
     }
-    for (int j = 0; j < k; ++j) gates[t * k + j] = renorm ? pe[j] / ssum : pe[j] / z;
+    if (j16 == 0 && t < T)
+        for (int j = 0; j < k; ++j) {
+            ids[t * k + j] = be_[j];
+            gates[t * k + j] = renorm ? pe[j] / ssum : pe[j] / z;
+        }
 }
 
 template <int NE, int TB, int KG>
@@ -300,8 +365,9 @@ hipError_t route(const void* x, const void* wg, const float* bias, int64_t T, in
                  int k, bool f32, bool renorm, int32_t* ids, float* gates, float* logits,
                  hipStream_t st) {
     if (f32) {
-        const dim3 grid((unsigned)((T + 127) / 128));
-        hipLaunchKernelGGL(route_f32, grid, dim3(128), 0, st, static_cast<const float*>(x),
+        const dim3 grid((unsigned)((T + RF_TOK - 1) / RF_TOK));
+        auto kernel = E <= 16 ? route_f32<1> : E <= 64 ? route_f32<4> : route_f32<16>;
+        hipLaunchKernelGGL(kernel, grid, dim3(RF_THREADS), 0, st, static_cast<const float*>(x),
                            static_cast<const float*>(wg), bias, T, d, E, k, (int)renorm, ids,
                            gates, logits);
         probe::mark("route_f32", st);

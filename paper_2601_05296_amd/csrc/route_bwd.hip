@@ -13,8 +13,8 @@
 //   dW_g = hi^T x + lo^T x          (K = tokens, split into chunks; the
 //                                    chunk partials and the two halves are
 //                                    summed in a fixed order)
-// f32 debug path: dl in float32, dx from LDS-staged dl rows, dW_g from
-// token-chunk partials, float32 FMA throughout.
+// f32 path: dl in float32, dx from LDS-staged dl rows (FMA), dW_g from
+// token-chunk partials (float32 matrix instructions).
 #include "common.hpp"
 #include "gemm.hpp"
 #include "gemm_rs.hpp"
@@ -24,7 +24,7 @@
 namespace moe {
 namespace {
 
-constexpr int RB_TOK = 32;        // tokens per workgroup in the dx kernel
+constexpr int RB_TOK = 16;        // tokens per workgroup in the f32 dx kernel
 constexpr int RB_CHUNK = 1024;    // least tokens per split in the dW_g kernels
 constexpr int RB_MAXSPLIT = 128;  // most splits: the partials stay O(E d), not O(T)
 constexpr int RB_EB = 32;         // experts per workgroup in the dW_g kernel
@@ -63,10 +63,10 @@ rb_dlogits(const float* __restrict__ dg, const float* __restrict__ logits,
     }
 }
 
-template <bool F32>
+// dx[t] (+)= sum_e dl[t][e] * W_g[e], one column per thread and RB_TOK tokens
 __global__ void __launch_bounds__(256)
-rb_dx(const float* __restrict__ dl, const void* __restrict__ wg_, int64_t T, int d, int E,
-      int accumulate, void* __restrict__ dx_) {
+rb_dx(const float* __restrict__ dl, const float* __restrict__ wg, int64_t T, int d, int E,
+      int accumulate, float* __restrict__ dx) {
     __shared__ float s_dl[RB_TOK][256];
     const int tid = threadIdx.x;
     const int64_t t0 = (int64_t)blockIdx.x * RB_TOK;
@@ -76,67 +76,78 @@ rb_dx(const float* __restrict__ dl, const void* __restrict__ wg_, int64_t T, int
         s_dl[tt][e] = tt < nt ? dl[(t0 + tt) * E + e] : 0.f;
     }
     __syncthreads();
-    for (int c = tid; c < d; c += 256) {
-        float acc[RB_TOK];
+    const int c = blockIdx.y * 256 + tid;
+    if (c >= d) return;
+    // the old values are all loaded before the first store: loads between the
+    // stores would wait for one another
+    float old[RB_TOK], acc[RB_TOK];
 #pragma unroll
-        for (int tt = 0; tt < RB_TOK; ++tt) acc[tt] = 0.f;
-        for (int e = 0; e < E; ++e) {
-            float w;
-            if (F32) w = static_cast<const float*>(wg_)[(int64_t)e * d + c];
-            else w = bf2f(static_cast<const bf16_t*>(wg_)[(int64_t)e * d + c]);
-#pragma unroll
-            for (int tt = 0; tt < RB_TOK; ++tt) acc[tt] = fmaf(s_dl[tt][e], w, acc[tt]);
-        }
-        for (int tt = 0; tt < nt; ++tt) {
-            const int64_t o = (t0 + tt) * d + c;
-            if (F32) {
-                float* p = static_cast<float*>(dx_) + o;
-                *p = accumulate ? *p + acc[tt] : acc[tt];
-            } else {
-                bf16_t* p = static_cast<bf16_t*>(dx_) + o;
-                const float v = accumulate ? bf2f(*p) + acc[tt] : acc[tt];
-                *p = (bf16_t)f2bf(v);
-            }
-        }
+    for (int tt = 0; tt < RB_TOK; ++tt) {
+        old[tt] = accumulate && tt < nt ? dx[(t0 + tt) * d + c] : 0.f;
+        acc[tt] = 0.f;
     }
+    for (int e = 0; e < E; ++e) {
+        const float w = wg[(int64_t)e * d + c];
+#pragma unroll
+        for (int tt = 0; tt < RB_TOK; ++tt) acc[tt] = fmaf(s_dl[tt][e], w, acc[tt]);
+    }
+#pragma unroll
+    for (int tt = 0; tt < RB_TOK; ++tt)
+        if (tt < nt) dx[(t0 + tt) * d + c] = accumulate ? old[tt] + acc[tt] : acc[tt];
 }
 
-template <bool F32>
-__global__ void __launch_bounds__(256)
-rb_dwg_partial(const float* __restrict__ dl, const void* __restrict__ x_, int64_t T, int d,
-               int E, int64_t chunk, float* __restrict__ part) {
-    __shared__ float s_dl[64][RB_EB];
-    const int tid = threadIdx.x;
-    const int c = blockIdx.x * 256 + tid;
-    const int e0 = blockIdx.y * RB_EB;
-    const int split = blockIdx.z;
-    const int64_t tlo = (int64_t)split * chunk;
-    const int64_t thi = min(T, tlo + chunk);
-    float acc[RB_EB];
+// part[split][e][c] = sum over the split's tokens of dl[t][e] * x[t][c], by
+// v_mfma_f32_32x32x2_f32 straight from global memory (both operands are rows of
+// a token: a lane half takes every other token). A workgroup owns 32 experts x
+// 32 columns of a split; its 16 waves take every 16th pair of tokens and meet in
+// LDS. Latency-bound: one thread per column with a serial token loop took 416 us
+// for T = 1024, E = 8, d = 256.
+constexpr int RBP_WAVES = 16;
+
+__global__ void __launch_bounds__(RBP_WAVES * WAVE)
+rb_dwg_partial(const float* __restrict__ dl, const float* __restrict__ x, int64_t T, int d, int E,
+               int64_t chunk, float* __restrict__ part) {
+    __shared__ float red[RBP_WAVES / 2][16][WAVE];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int c = blockIdx.x * 32 + (lane & 31), e = blockIdx.y * RB_EB + (lane & 31);
+    const int64_t tlo = (int64_t)blockIdx.z * chunk, thi = min(T, tlo + chunk);
+    f32x16 acc;
 #pragma unroll
-    for (int i = 0; i < RB_EB; ++i) acc[i] = 0.f;
-    for (int64_t tb = tlo; tb < thi; tb += 64) {
-        __syncthreads();
-        for (int i = tid; i < 64 * RB_EB; i += 256) {
-            const int tt = i / RB_EB, ee = i % RB_EB;
-            const int64_t t = tb + tt;
-            s_dl[tt][ee] = (t < thi && e0 + ee < E) ? dl[t * E + e0 + ee] : 0.f;
-        }
-        __syncthreads();
-        const int ntt = (int)min((int64_t)64, thi - tb);
-        if (c < d) {
-            for (int tt = 0; tt < ntt; ++tt) {
-                const int64_t o = (tb + tt) * d + c;
-                const float xv = F32 ? static_cast<const float*>(x_)[o]
-                                     : bf2f(static_cast<const bf16_t*>(x_)[o]);
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    const bool ok = e < E;
+    constexpr int U = 4;   // steps in flight (16: 12.9 us against 11.2)
+    for (int64_t t = tlo + 2 * wv + (lane >> 5); t - (lane >> 5) < thi; t += 2 * RBP_WAVES * U) {
+        float a[U], b[U];
 #pragma unroll
-                for (int ee = 0; ee < RB_EB; ++ee) acc[ee] = fmaf(s_dl[tt][ee], xv, acc[ee]);
-            }
+        for (int u = 0; u < U; ++u) {
+            const int64_t tu = t + 2 * RBP_WAVES * u;
+            const bool in = tu < thi;
+            a[u] = in && ok ? dl[tu * E + e] : 0.f;
+            b[u] = in ? x[tu * d + c] : 0.f;
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[u], a[u], acc, 0, 0, 0);
     }
-    if (c < d)
-        for (int ee = 0; ee < RB_EB && e0 + ee < E; ++ee)
-            part[((int64_t)split * E + e0 + ee) * d + c] = acc[ee];
+    // halves of the waves add up pairwise; lane holds expert lane % 32, columns
+    // 8 * (r / 4) + 4 * (lane / 32) + r % 4
+    for (int n = RBP_WAVES / 2; n > 0; n >>= 1) {
+        if (wv >= n && wv < 2 * n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) red[wv - n][r][lane] = acc[r];
+        __syncthreads();
+        if (wv < n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] += red[wv][r][lane];
+        __syncthreads();
+    }
+    if (wv == 0 && ok) {
+        float* o = part + ((int64_t)blockIdx.z * E + e) * d + blockIdx.x * 32 + 4 * (lane >> 5);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4*>(o + 8 * q) =
+                f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    }
 }
 
 __global__ void rb_dwg_reduce(const float* __restrict__ part, int nsplit, int E, int d,
@@ -365,13 +376,15 @@ hipError_t route_bwd(const float* dgates, const float* logits, const int32_t* id
         hipLaunchKernelGGL(rb_dlogits, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, st, dgates,
                            logits, ids, gates, T, E, k, (int)renorm, dl);
         probe::mark("rb_dlogits", st);
-        hipLaunchKernelGGL(rb_dx<true>, dim3((unsigned)((T + RB_TOK - 1) / RB_TOK)), dim3(256), 0,
-                           st, dl, wg, T, d, E, (int)accumulate, dx);
+        hipLaunchKernelGGL(rb_dx, dim3((unsigned)((T + RB_TOK - 1) / RB_TOK), (unsigned)((d + 255) / 256)),
+                           dim3(256), 0, st, dl, static_cast<const float*>(wg), T, d, E,
+                           (int)accumulate, static_cast<float*>(dx));
         probe::mark("rb_dx", st);
         const int ns = nsplits(T);
-        hipLaunchKernelGGL(rb_dwg_partial<true>,
-                           dim3((unsigned)((d + 255) / 256), (unsigned)((E + RB_EB - 1) / RB_EB), (unsigned)ns),
-                           dim3(256), 0, st, dl, x, T, d, E, split_tokens(T, RB_CHUNK), part);
+        hipLaunchKernelGGL(rb_dwg_partial,
+                           dim3((unsigned)(d / 32), (unsigned)((E + RB_EB - 1) / RB_EB), (unsigned)ns),
+                           dim3(RBP_WAVES * WAVE), 0, st, dl, static_cast<const float*>(x), T, d, E,
+                           split_tokens(T, RB_CHUNK), part);
         probe::mark("rb_dwg_partial", st);
         hipLaunchKernelGGL(rb_dwg_reduce, dim3((unsigned)(((int64_t)E * d + 255) / 256)), dim3(256), 0,
                            st, part, ns, E, d, dwg);
