@@ -62,6 +62,13 @@ template <int ACT> using CFirst = std::conditional_t<ACT == ACT_SWIGLU, RD, RS>;
 // it costs two transcendentals and some ten other vector operations, about
 // as much vector-ALU time per slice as the slice's MFMAs take).
 using RHW = rs::Cfg<128, 512, 2, 4, 1>;
+// Smaller tiles for launches that would leave CUs idle (the choice between them
+// and the large ones is at few_tiles): h formed on load in half the rows, and a
+// quarter of the weight-gradient tile on four waves, two workgroups per CU.
+using RHN = rs::Cfg<64, 512, 1, 8, 1>;
+using RDN = rs::Cfg<128, 64, 2, 2, 2>;
+using RSN = rs::Cfg<128, 128, 2, 2, 1>;
+template <int ACT> using CNarrow = std::conditional_t<ACT == ACT_SWIGLU, RDN, RSN>;
 static_assert(RD::THREADS == RS::THREADS && RD::LDS == RS::LDS, "RD and RS launch alike");
 
 // ============================ kernels ==============================================
@@ -171,14 +178,13 @@ struct HKC {
 };
 
 // G2 with h formed on load: O = h W2[e] from the saved A (and B), no h buffer.
-template <int ACT, bool SCATTER>
-__global__ void __launch_bounds__(RHW::THREADS)
+template <int ACT, bool SCATTER, class C>
+__global__ void __launch_bounds__(C::THREADS)
 g2h_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
            const bf16_t* __restrict__ w2, const int32_t* __restrict__ offsets, int d, int f,
            int E, int n_base, int ncols, int64_t ldo, bf16_t* __restrict__ O,
            const int32_t* __restrict__ tok, const float* __restrict__ gs) {
     extern __shared__ __align__(16) char lds[];
-    using C = RHW;
     SlotTile t;
     const int NT = (ncols + C::BN - 1) / C::BN;
     if (!find_slot_tile<C::THREADS>(reinterpret_cast<int*>(lds), offsets, E, C::BM, NT,
@@ -381,12 +387,12 @@ __device__ __forceinline__ void st_dw(float* p, const f32x4& v, int add) {
 }
 
 // G3: dW2[e] = sum_s HG[s]^T dY[eti[s]]   (M = f, N = d, K = slots of e)
-__global__ void __launch_bounds__(RS::THREADS)
+template <class C>
+__global__ void __launch_bounds__(C::THREADS, 2)
 g3_kernel(const bf16_t* __restrict__ HG, const bf16_t* __restrict__ dy,
           const ExpertRank* __restrict__ rank, const int32_t* __restrict__ eti, int d, int f,
           int add, float* __restrict__ dw2) {
     extern __shared__ __align__(16) char lds[];
-    using C = RS;
     const int MT = (f + C::BM - 1) / C::BM, NT = (d + C::BN - 1) / C::BN;
     ExpertRank er;
     int mt, nt;
@@ -495,14 +501,13 @@ __global__ void zero_bf16(bf16_t* __restrict__ p, int64_t n) {
 // G3 with g*h formed on load from the saved A (and B) and the slot-ordered
 // gates gs: dW2[e] = sum_s (g h)[s]^T dY[eti[s]]. Runs before G4, which then
 // writes dA, dB over A, B and no g*h.
-template <int ACT>
-__global__ void __launch_bounds__(RHW::THREADS)
+template <int ACT, class C>
+__global__ void __launch_bounds__(C::THREADS)
 g3h_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
            const float* __restrict__ gs, const bf16_t* __restrict__ dy,
            const ExpertRank* __restrict__ rank, const int32_t* __restrict__ eti, int d, int f,
            int add, float* __restrict__ dw2) {
     extern __shared__ __align__(16) char lds[];
-    using C = RHW;
     const int MT = (f + C::BM - 1) / C::BM, NT = (d + C::BN - 1) / C::BN;
     ExpertRank er;
     int mt, nt;
@@ -528,14 +533,13 @@ g3h_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
 
 // G5: dW1[e] = x[eti]^T dA, dW3[e] = x[eti]^T dB   (M = d, N = f, K = slots of e)
 // (non-gated: dW1 alone)
-template <int ACT>
-__global__ void __launch_bounds__(RD::THREADS)
+template <int ACT, class C>
+__global__ void __launch_bounds__(C::THREADS, 2)
 g5_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dA,
           const bf16_t* __restrict__ dB, const ExpertRank* __restrict__ rank,
           const int32_t* __restrict__ eti, int d, int f, int add, float* __restrict__ dw1,
           float* __restrict__ dw3) {
     extern __shared__ __align__(16) char lds[];
-    using C = CFirst<ACT>;
     const int MT = (d + C::BM - 1) / C::BM, NT = (f + C::BN - 1) / C::BN;
     ExpertRank er;
     int mt, nt;
@@ -650,10 +654,9 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 //    GEMM there: r = 96 (127, 103), 9 (526, 374); E = 8, d = 4096, f = 14336:
 //    r = 112 (219, 202), 150 (230, 315).
 //  - the second GEMM and the dX GEMM (N = d, K = f or 2f) leave the chip half
-//    idle in 256 x 256 tiles when the experts are few: 128-row tiles then up to
-//    r = 256 (dX, E = 8, d = 4096, f = 14336: r = 32 (487, 332), 150 (538, 447);
+//    idle in 256 x 256 tiles when the experts are few: 128-row tiles then (dX, E = 8, d = 4096, f = 14336: r = 32 (487, 332), 150 (538, 447);
 //    E = 16, d = 1024, f = 4096: r = 200 (153, 89)).
-//  - columns: the widest tiles if they give 192 workgroups; the dX and second
+//  - columns: the widest tiles if they give 128 workgroups; the dX and second
 //    GEMMs, with longer K and fewer columns, take 128 columns while those tiles
 //    run in one round (E = 8: 330 against 400 of the wide ones) and 64 while
 //    those do (E = 16: 55 against 65 and 95).
@@ -667,12 +670,26 @@ inline int64_t est_rows(int64_t S, int E, int BM) {   // tile rows of BM
     const int64_t act = S < E ? S : E, full = (S + act * BM / 3) / BM;
     return act > full ? act : full;
 }
-// first GEMM and dh GEMM: N = f, K = d
-inline SmallTile small_wide_n(int64_t S, int E, int ncols, int wide_cols) {
+//  - half-idle launches at any r: with 4 experts, d = 512, f = 2048 a 256-row
+//    tile's grid has 16 (T = 2000) to 66 (T = 8192) tiles in the second and dX
+//    GEMMs. dX, T = 2000 and 8192: (84, 34), (86, 70), 16384 (99, 143); second in
+//    RHW and RHN: (63, 42), (65, 49), 16384 (75, 98); E = 8, d = 4096, f = 14336,
+//    T = 600 (418, 307), 1000 (424, 625). Weight gradients, T = 8192: dW2 (71, 50),
+//    dW1 and dW3 (61, 47), non-gated (55, 29); E = 16, d = 1024, f = 4096 (1024
+//    tiles): dW2 (102, 110). Smaller dW1 / dW3 tiles also where the experts have
+//    up to 96 slots, a slice or two of K: E = 64, d = 2048, f = 1408, r = 19 (281,
+//    258), 96 (312, 293), 159 (363, 386).
+inline bool few_tiles(int64_t tiles) { return tiles <= 128; }
+// first GEMM and dh GEMM: N = f, K = d; wide_cols and big_cols columns per tile
+// in the wide small tiles and in the 256-row ones
+inline SmallTile small_wide_n(int64_t S, int E, int ncols, int wide_cols, int big_cols) {
     const int64_t r = S / E;
-    const int rows = r <= 40 ? 64 : r <= 112 ? 128 : 0;
+    const bool few = est_rows(S, E, 256) * cdiv(ncols, big_cols) <= 80;
+    const int rows = r <= 40 || (few && est_rows(S, E, 64) * cdiv(ncols, 128) <= 256) ? 64
+                     : r <= 112 || few                                               ? 128
+                                                                                     : 0;
     if (!rows) return {0, 0};
-    return {rows, est_rows(S, E, rows) * cdiv(ncols, wide_cols) >= 192 ? SMALL_WIDE : SMALL_NARROW};
+    return {rows, est_rows(S, E, rows) * cdiv(ncols, wide_cols) >= 128 ? SMALL_WIDE : SMALL_NARROW};
 }
 inline int small_level(int64_t mt, int ncols) {
     return mt * cdiv(ncols, 64) <= 256 ? SMALL_SLIM : mt * cdiv(ncols, 128) <= 256 ? SMALL_NARROW : SMALL_WIDE;
@@ -680,8 +697,10 @@ inline int small_level(int64_t mt, int ncols) {
 // second GEMM from the h buffer, and dX GEMM: N = d
 inline SmallTile small_long_k(int64_t S, int E, int ncols) {
     const int64_t r = S / E;
-    const bool few = r <= 256 && est_rows(S, E, RS::BM) * cdiv(ncols, RS::BN) <= 128;
-    const int rows = r <= 40 ? 64 : r <= 112 || few ? 128 : 0;
+    const bool few = few_tiles(est_rows(S, E, RS::BM) * cdiv(ncols, RS::BN));
+    const int rows = r <= 40 || (few && est_rows(S, E, 64) * cdiv(ncols, 128) <= 256) ? 64
+                     : r <= 112 || few                                               ? 128
+                                                                                     : 0;
     if (!rows) return {0, 0};
     return {rows, small_level(est_rows(S, E, rows), ncols)};
 }
@@ -707,17 +726,22 @@ hipError_t set_lds_limits() {
             set(reinterpret_cast<const void*>(g1_kernel<ACT>), CFirst<ACT>::LDS);
             set(reinterpret_cast<const void*>(g4_kernel<ACT, true>), RS::LDS);
             set(reinterpret_cast<const void*>(g4_kernel<ACT, false>), RS::LDS);
-            set(reinterpret_cast<const void*>(g5_kernel<ACT>), CFirst<ACT>::LDS);
-            set(reinterpret_cast<const void*>(g2h_kernel<ACT, false>), RHW::LDS);
-            set(reinterpret_cast<const void*>(g2h_kernel<ACT, true>), RHW::LDS);
-            set(reinterpret_cast<const void*>(g3h_kernel<ACT>), RHW::LDS);
+            set(reinterpret_cast<const void*>(g5_kernel<ACT, CFirst<ACT>>), CFirst<ACT>::LDS);
+            set(reinterpret_cast<const void*>(g5_kernel<ACT, CNarrow<ACT>>), CNarrow<ACT>::LDS);
+            set(reinterpret_cast<const void*>(g2h_kernel<ACT, false, RHW>), RHW::LDS);
+            set(reinterpret_cast<const void*>(g2h_kernel<ACT, true, RHW>), RHW::LDS);
+            set(reinterpret_cast<const void*>(g2h_kernel<ACT, false, RHN>), RHN::LDS);
+            set(reinterpret_cast<const void*>(g2h_kernel<ACT, true, RHN>), RHN::LDS);
+            set(reinterpret_cast<const void*>(g3h_kernel<ACT, RHW>), RHW::LDS);
+            set(reinterpret_cast<const void*>(g3h_kernel<ACT, RHN>), RHN::LDS);
         };
         per_act(std::integral_constant<int, ACT_SWIGLU>{});
         per_act(std::integral_constant<int, ACT_SILU>{});
         per_act(std::integral_constant<int, ACT_RELU>{});
         set(reinterpret_cast<const void*>(g2_kernel<false>), RS::LDS);
         set(reinterpret_cast<const void*>(g2_kernel<true>), RS::LDS);
-        set(reinterpret_cast<const void*>(g3_kernel), RS::LDS);
+        set(reinterpret_cast<const void*>(g3_kernel<RS>), RS::LDS);
+        set(reinterpret_cast<const void*>(g3_kernel<RSN>), RSN::LDS);
         set(reinterpret_cast<const void*>(g6_kernel<false>), RS::LDS);
         set(reinterpret_cast<const void*>(g6_kernel<true>), RS::LDS);
         return e;
@@ -779,10 +803,9 @@ hipError_t ffn_fwd_act(const FfnArgs& a, hipStream_t st) {
     const int64_t S = a.T * a.k;
     if (hipError_t e = set_lds_limits(); e != hipSuccess) return e;
     using C1 = CFirst<ACT>;
-    using C2H = RHW;
     // h buffered between the GEMMs, or (h_on_load) formed again from A, B
     bf16_t* H = a.h_on_load ? nullptr : static_cast<bf16_t*>(a.ws);
-    const SmallTile t1 = small_wide_n(S, a.E, a.f, ACT == ACT_SWIGLU ? 128 : 256);
+    const SmallTile t1 = small_wide_n(S, a.E, a.f, ACT == ACT_SWIGLU ? 128 : 256, CFirst<ACT>::BN);
     if (t1.rows) {
         if (hipError_t e = small_first(a, t1, H, st); e != hipSuccess) return e;
     } else {
@@ -798,11 +821,16 @@ hipError_t ffn_fwd_act(const FfnArgs& a, hipStream_t st) {
         const SmallTile t2 = H ? small_long_k(S, a.E, nc) : small_form_h(S, a.E, nc);
         if (t2.rows) return small_second(a, t2, H, c0, nc, ldo, out, gs, st);
         if (a.h_on_load) {
-            auto g2h = gs ? g2h_kernel<ACT, true> : g2h_kernel<ACT, false>;
-            hipLaunchKernelGGL(g2h, dim3(slot_grid(S, a.E, C2H::BM, cdiv(nc, C2H::BN))),
-                               dim3(C2H::THREADS), C2H::LDS, st, (const bf16_t*)a.A,
-                               (const bf16_t*)a.B, (const bf16_t*)a.w2, a.offsets, a.d, a.f, a.E,
-                               c0, nc, ldo, out, a.eti, gs);
+            auto run = [&](auto cfg) {
+                using C = decltype(cfg);
+                auto g2h = gs ? g2h_kernel<ACT, true, C> : g2h_kernel<ACT, false, C>;
+                hipLaunchKernelGGL(g2h, dim3(slot_grid(S, a.E, C::BM, cdiv(nc, C::BN))),
+                                   dim3(C::THREADS), C::LDS, st, (const bf16_t*)a.A,
+                                   (const bf16_t*)a.B, (const bf16_t*)a.w2, a.offsets, a.d, a.f,
+                                   a.E, c0, nc, ldo, out, a.eti, gs);
+            };
+            if (few_tiles(est_rows(S, a.E, RHW::BM) * cdiv(nc, RHW::BN))) run(RHN{});
+            else run(RHW{});
             probe::mark("g2h_kernel", st);
         } else {
             auto g2 = gs ? g2_kernel<true> : g2_kernel<false>;
@@ -847,7 +875,7 @@ template <int ACT>
 hipError_t ffn_first_act(const FfnArgs& a, hipStream_t st) {
     const int64_t S = a.T * a.k;
     if (hipError_t e = set_lds_limits(); e != hipSuccess) return e;
-    if (const SmallTile t1 = small_wide_n(S, a.E, a.f, ACT == ACT_SWIGLU ? 128 : 256); t1.rows)
+    if (const SmallTile t1 = small_wide_n(S, a.E, a.f, ACT == ACT_SWIGLU ? 128 : 256, CFirst<ACT>::BN); t1.rows)
         return small_first(a, t1, nullptr, st);
     using C1 = CFirst<ACT>;
     hipLaunchKernelGGL(g1_kernel<ACT>, dim3(slot_grid(S, a.E, C1::BM, cdiv(a.f, C1::BN))),
@@ -906,8 +934,6 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
     const int64_t S = a.T * a.k;
     constexpr bool GATED = ACT == ACT_SWIGLU;
     if (hipError_t e = set_lds_limits(); e != hipSuccess) return e;
-    using C5 = CFirst<ACT>;
-    using C3H = RHW;
     const int nparts = g4_nparts(a.f);
     float* part = static_cast<float*>(a.ws);
     char* const ws2 = static_cast<char*>(a.ws) + align256((size_t)S * nparts * sizeof(float));
@@ -929,13 +955,18 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
         hipLaunchKernelGGL(slot_gates, grid1d(S, 256), dim3(256), 0, st, a.gates,
                            a.slot_src, a.offsets, a.E, S, gs);
         probe::mark("slot_gates", st);
-        hipLaunchKernelGGL(g3h_kernel<ACT>, dim3(wgrad_grid(a.E, cdiv(a.f, C3H::BM), cdiv(a.d, C3H::BN))),
-                           dim3(C3H::THREADS), C3H::LDS, st, (const bf16_t*)a.A,
-                           (const bf16_t*)Bx, (const float*)gs, (const bf16_t*)a.dy, rank,
-                           a.eti, a.d, a.f, (int)a.accumulate_dw, a.dw2);
+        auto run = [&](auto cfg) {
+            using C = decltype(cfg);
+            hipLaunchKernelGGL((g3h_kernel<ACT, C>), dim3(wgrad_grid(a.E, cdiv(a.f, C::BM), cdiv(a.d, C::BN))),
+                               dim3(C::THREADS), C::LDS, st, (const bf16_t*)a.A, (const bf16_t*)Bx,
+                               (const float*)gs, (const bf16_t*)a.dy, rank, a.eti, a.d, a.f,
+                               (int)a.accumulate_dw, a.dw2);
+        };
+        if (few_tiles((int64_t)a.E * cdiv(a.f, RHW::BM) * cdiv(a.d, RHW::BN))) run(RHN{});
+        else run(RHW{});
         probe::mark("g3h_kernel", st);
     }
-    const SmallTile t4 = small_wide_n(S, a.E, a.f, 256);
+    const SmallTile t4 = small_wide_n(S, a.E, a.f, 256, RS::BN);
     if (t4.rows) {
         if (hipError_t e = small_dact(a, t4, gs, HG, part, nparts, st); e != hipSuccess) return e;
     } else {
@@ -950,15 +981,28 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
         e != hipSuccess)
         return e;
     if (!a.h_on_load) {
-        hipLaunchKernelGGL(g3_kernel, dim3(wgrad_grid(a.E, cdiv(a.f, RS::BM), cdiv(a.d, RS::BN))),
-                           dim3(RS::THREADS), RS::LDS, st, (const bf16_t*)HG, (const bf16_t*)a.dy,
-                           rank, a.eti, a.d, a.f, (int)a.accumulate_dw, a.dw2);
+        auto run = [&](auto cfg) {
+            using C = decltype(cfg);
+            hipLaunchKernelGGL(g3_kernel<C>, dim3(wgrad_grid(a.E, cdiv(a.f, C::BM), cdiv(a.d, C::BN))),
+                               dim3(C::THREADS), C::LDS, st, (const bf16_t*)HG,
+                               (const bf16_t*)a.dy, rank, a.eti, a.d, a.f, (int)a.accumulate_dw,
+                               a.dw2);
+        };
+        if (few_tiles((int64_t)a.E * cdiv(a.f, RS::BM) * cdiv(a.d, RS::BN))) run(RSN{});
+        else run(RS{});
         probe::mark("g3_kernel", st);
     }
-    hipLaunchKernelGGL(g5_kernel<ACT>, dim3(wgrad_grid(a.E, cdiv(a.d, C5::BM), cdiv(a.f, C5::BN))),
-                       dim3(C5::THREADS), C5::LDS, st, (const bf16_t*)a.x, (const bf16_t*)a.A,
-                       (const bf16_t*)a.B, rank, a.eti, a.d, a.f, (int)a.accumulate_dw,
-                       a.dw1, a.dw3);
+    auto dw13 = [&](auto cfg) {
+        using C = decltype(cfg);
+        hipLaunchKernelGGL((g5_kernel<ACT, C>), dim3(wgrad_grid(a.E, cdiv(a.d, C::BM), cdiv(a.f, C::BN))),
+                           dim3(C::THREADS), C::LDS, st, (const bf16_t*)a.x, (const bf16_t*)a.A,
+                           (const bf16_t*)a.B, rank, a.eti, a.d, a.f, (int)a.accumulate_dw, a.dw1,
+                           a.dw3);
+    };
+    if (S / a.E <= 96 ||
+        few_tiles((int64_t)a.E * cdiv(a.d, CFirst<ACT>::BM) * cdiv(a.f, CFirst<ACT>::BN)))
+        dw13(CNarrow<ACT>{});
+    else dw13(CFirst<ACT>{});
     probe::mark("g5_kernel", st);
     const int kslices = (GATED ? 2 : 1) * a.f / rs::KS;
     auto t6 = [&](int nc) { return small_long_k(S, a.E, nc); };

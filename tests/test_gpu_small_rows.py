@@ -90,7 +90,13 @@ EDGES_128 = [97, 127, 128, 129, 1, 64, 65, 100]        # mean 88: 128-row tiles
     (EDGES_64 * 8, 192, 320, "swiglu", True, False),
     (EDGES_64 * 24, 576, 576, "silu", False, True),
     (EDGES_128 * 12, 576, 576, "swiglu", False, False),
-    (EDGES_128 * 12, 64, 64, "swiglu", True, True)])
+    (EDGES_128 * 12, 64, 64, "swiglu", True, True),
+    # many rows of few experts: launches that leave CUs idle in the large tiles
+    # (dX and second GEMM in 64- and 128-row tiles, h on load in 64 x 512, weight
+    # gradients in 128 x 128)
+    ([700, 513], 320, 576, "swiglu", True, False),
+    ([2049, 1, 1500], 192, 704, "silu", False, False),
+    ([6000, 5000], 576, 192, "relu", True, True)])
 def test_small_rows_same_bits(counts, d, f, act, h_on_load, atomic):
     E, T = len(counts), sum(counts)
     rng = np.random.Generator(np.random.PCG64(T + d + f))
@@ -100,9 +106,9 @@ def test_small_rows_same_bits(counts, d, f, act, h_on_load, atomic):
          _bf16(rng, (E, f, d), f ** -0.5))
     gates = torch.from_numpy(rng.random((T, 1), dtype=np.float32)).cuda()
     one = _ffn(ids, gates, x, dy, w, act, h_on_load, atomic)
-    # repeats for a mean of 300 rows per expert and 100 row tiles of 128, beyond
+    # repeats for a mean of 300 rows per expert and 130 row tiles of 256, beyond
     # every rule of the small kernels
-    n = -(-max(300 * E, 100 * 128) // T)
+    n = -(-max(300 * E, 130 * 256) // T)
     rep = _ffn(np.tile(ids, (n, 1)), gates.repeat(n, 1), x.repeat(n, 1), dy.repeat(n, 1), w, act,
                h_on_load, atomic)
     for name, a in one.items():
