@@ -404,6 +404,8 @@ def kernel_model(name, cfg, elem, recompute=False):
     T, d, f, E, k = cfg.T, cfg.d, cfg.f, cfg.E, cfg.k
     S = T * k
     g = 2.0 * S * d * f  # flops of one [S x d] x [d x f] product
+    if name.startswith("sk_g"):   # the same GEMM in its small-row tiles
+        name = name[3:] + "_kernel"
     nb = 2 if cfg.act == "swiglu" else 1   # right operands of g1, g5, g6
     flops = {"g1_kernel": nb * g * (2 if recompute else 1), "g2_kernel": g, "g2h_kernel": g,
              "g3_kernel": g, "g3h_kernel": g,
@@ -419,13 +421,12 @@ def kernel_model(name, cfg, elem, recompute=False):
         "tile_rank": nbuild * (S * 4 + 3 * S * 4),
         "combine": 2 * (S * d * elem + T * d * elem + T * k * 8),   # forward and backward
         "dgate_reduce": S * nparts * 4 + S * 8,
-        "slot_gates": S * 12,
-        "fwd_slot_gates": S * 12,
-        "zero_bf16": 2 * T * d * elem,   # y in the forward, dx in the backward
-        "expert_ranks": E * 4 + E * 16,
+        "index_one": nbuild * (S * 4 + 3 * S * 4),
+        "fwd_prep": S * 12 + T * d * elem,   # slot gates, y cleared
+        "bwd_prep": E * 4 + E * 16 + S * 12,
+        "zero_bf16": T * d * elem,           # dx
         "rb_dlogits": T * E * 4 * 2 + T * k * 12,
-        "rb_dx": T * E * 4 + E * d * elem + 2 * T * d * elem,
-        "rb_dwg_partial": T * E * 4 + T * d * elem,
+        "rb_products": 2 * T * E * 4 + E * d * elem + 3 * T * d * elem,
         "rb_dwg_reduce": 0,
     }
     return float(byts.get(name, 0)), "GB/s", "hbm"
@@ -932,11 +933,11 @@ def main():
                 "frac": kd["frac"], "traffic": read_traffic(cfg.name, dom), "kernel": dom,
                 "per_launch": kd["per_launch"], "avg_ms": kd["avg_ms"],
                 "launches_per_step": kd["launches_per_step"]}
-    gemm_ms = sum(kernels[n]["ms_per_step"] for n in kernels if n.startswith("g") and n[1].isdigit())
+    gemm_ms = sum(kernels[n]["ms_per_step"] for n in kernels if n.startswith("sk_g") or (n.startswith("g") and n[1].isdigit()))
     # per-stage kernel time (ms per step); the router's two stages are the part
     # a sparse-to-sparse timing leaves out
-    stage_of = {"route": ("route_",), "build": ("tile_",), "ffn_fwd": ("g1_", "g2_", "g2h_", "f32_g1", "f32_g2"),
-                "combine": ("combine", "zero_", "fwd_slot_gates"), "ffn_bwd": ("g3_", "g3h_", "g4_", "g5_", "g6_", "dgate", "slot_gates", "expert_ranks", "f32_g3",
+    stage_of = {"route": ("route_",), "build": ("tile_", "index_one"), "ffn_fwd": ("g1_", "g2_", "g2h_", "sk_g1", "sk_g2", "f32_g1", "f32_g2"),
+                "combine": ("combine", "zero_", "fwd_prep"), "ffn_bwd": ("g3_", "g3h_", "g4_", "g5_", "g6_", "sk_g4", "sk_g6", "dgate", "bwd_prep", "f32_g3",
                                                       "f32_g4", "f32_g5", "f32_g6"),
                 "route_bwd": ("rb_",)}
     stages = {st: round(sum(v["ms_per_step"] for n, v in kernels.items()

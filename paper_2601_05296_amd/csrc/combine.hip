@@ -124,7 +124,9 @@ void launch_combine(const void* src, int64_t src_ld, const float* w, const int32
     // most one wave per token instead, so that no lane idles and each lane
     // keeps more source loads in flight (measured faster on both).
     const bool pow2 = (nchunk & (nchunk - 1)) == 0;
-    const int cap = (!pow2 || k > 4) ? WAVE : CMB_THREADS;
+    // With few tokens the launch is bound by the latency of one lane's loop: a
+    // whole workgroup per token then (T = 1, k = 6, d = 2048: 9.3 us with one wave).
+    const int cap = T >= 2048 && (!pow2 || k > 4) ? WAVE : CMB_THREADS;
     int lpt_log2 = 0;
     while ((1 << lpt_log2) < nchunk && (1 << lpt_log2) < cap) ++lpt_log2;
     const int64_t tpb = CMB_THREADS >> lpt_log2;

@@ -466,36 +466,68 @@ struct GHMC {
     }
 };
 
-// gs[s] = gates[slot_src[s]] for the filled slots s < offsets[E], 0 for the
-// rest up to S (the gate of each slot in slot order, for the dW2 GEMM's
-// left operand; fewer than S slots are filled only when the index build
-// rejected choices)
-__global__ void slot_gates(const float* __restrict__ gates, const int32_t* __restrict__ slot_src,
-                           const int32_t* __restrict__ offsets, int E, int64_t S,
-                           float* __restrict__ gs) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < offsets[E]) gs[s] = gates[slot_src[s]];
-    else if (s < S) gs[s] = 0.0f;
-}
-
-// gs[token_index_map[i]] = gates[i] for the accepted choices i < T*k: the
-// gate of each filled slot in slot order, from the token-side map (the
-// forward has no slot_src)
-__global__ void fwd_slot_gates(const float* __restrict__ gates,
-                                    const int32_t* __restrict__ tim, int64_t n,
-                                    float* __restrict__ gs) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        const int32_t s = tim[i];
-        if (s >= 0) gs[s] = gates[i];
-    }
-}
+// The small preparations of the forward's and the backward's GEMMs, each in one
+// launch (a launch of their own took 3 to 5 us each, whatever its work).
 
 // p[0..n) = 0 for n bf16 values, n a multiple of 8, p 16-byte aligned (a
 // kernel rather than a memset, so that it can be captured in a graph)
-__global__ void zero_bf16(bf16_t* __restrict__ p, int64_t n) {
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8;
-    if (i < n) st16(p + i, uint4{0u, 0u, 0u, 0u});
+__device__ __forceinline__ void clear_bf16(bf16_t* __restrict__ p, int64_t n, int64_t i,
+                                           int64_t step) {
+    for (; i * 8 < n; i += step) st16(p + i * 8, uint4{0u, 0u, 0u, 0u});
+}
+__global__ void __launch_bounds__(256) zero_bf16(bf16_t* __restrict__ p, int64_t n) {
+    clear_bf16(p, n, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
+}
+
+// gs[token_index_map[i]] = gates[i] for the accepted choices i < S: the gate of
+// each filled slot in slot order, from the token-side map (the forward has no
+// slot_src); y[0..n) = 0
+__global__ void __launch_bounds__(256)
+fwd_prep(const float* __restrict__ gates, const int32_t* __restrict__ tim, int64_t S,
+         float* __restrict__ gs, bf16_t* __restrict__ y, int64_t n) {
+    const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+    for (int64_t i = i0; i < S; i += step) {
+        const int32_t s = tim[i];
+        if (s >= 0) gs[s] = gates[i];
+    }
+    clear_bf16(y, n, i0, step);
+}
+
+// rank[r] = (expert, first slot, slot count) of the expert of rank r by slot
+// count, descending, ties to the lower index: the order in which the
+// weight-gradient GEMMs take the experts (wgrad_tile). One thread per expert of
+// one workgroup.
+__device__ __forceinline__ void expert_ranks(const int32_t* __restrict__ offsets, int E,
+                                             ExpertRank* __restrict__ rank) {
+    __shared__ int cnt[256];
+    const int t = threadIdx.x;
+    if (t < E) cnt[t] = offsets[t + 1] - offsets[t];
+    __syncthreads();
+    if (t >= E) return;
+    const int c = cnt[t];
+    int r = 0;
+    for (int u = 0; u < E; ++u) {
+        const int cu = cnt[u];
+        r += (cu > c) | ((cu == c) & (u < t));
+    }
+    rank[r] = ExpertRank{t, offsets[t], c, 0};
+}
+
+// Block 0: the experts' order. The others (with gs): gs[s] = gates[slot_src[s]] for
+// the filled slots s < offsets[E] and 0 for the rest up to S (the gate of each slot
+// in slot order, for the dW2 GEMM's left operand; fewer than S slots are filled
+// only when the index build rejected choices)
+__global__ void __launch_bounds__(256)
+bwd_prep(const float* __restrict__ gates, const int32_t* __restrict__ slot_src,
+         const int32_t* __restrict__ offsets, int E, int64_t S, ExpertRank* __restrict__ rank,
+         float* __restrict__ gs) {
+    if (blockIdx.x == 0) {
+        expert_ranks(offsets, E, rank);
+        return;
+    }
+    const int64_t filled = offsets[E], step = (int64_t)(gridDim.x - 1) * 256;
+    for (int64_t s = (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x; s < S; s += step)
+        gs[s] = s < filled ? gates[slot_src[s]] : 0.0f;
 }
 
 // G3 with g*h formed on load from the saved A (and B) and the slot-ordered
@@ -592,26 +624,6 @@ g6_kernel(const bf16_t* __restrict__ dA, const bf16_t* __restrict__ dB,
     slot_rows<SCATTER, C>(acc, t, ncols, ldo, dX, tok, nullptr, lds);
 }
 
-// rank[r] = (expert, first slot, slot count) of the expert of rank r by slot
-// count, descending, ties to the lower index: the order in which the
-// weight-gradient GEMMs take the experts (wgrad_tile). One workgroup, one
-// thread per expert.
-__global__ void __launch_bounds__(256)
-expert_ranks(const int32_t* __restrict__ offsets, int E, ExpertRank* __restrict__ rank) {
-    __shared__ int cnt[256];
-    const int t = threadIdx.x;
-    if (t < E) cnt[t] = offsets[t + 1] - offsets[t];
-    __syncthreads();
-    if (t >= E) return;
-    const int c = cnt[t];
-    int r = 0;
-    for (int u = 0; u < E; ++u) {
-        const int cu = cnt[u];
-        r += (cu > c) | ((cu == c) & (u < t));
-    }
-    rank[r] = ExpertRank{t, offsets[t], c, 0};
-}
-
 // d_gates[slot_src[s]] = sum of the G4 partials of slot s (fixed order)
 // (16-byte loads when a slot's nparts partials fill whole 16-byte vectors;
 // the sum runs in order p = 0..nparts-1 either way)
@@ -635,6 +647,12 @@ __global__ void dgate_reduce(const float* __restrict__ part, int nparts,
 }
 
 inline dim3 grid1d(int64_t n, int bs) { return dim3((unsigned)((n + bs - 1) / bs)); }
+
+// workgroups of a preparation launch over S slots and n bf16 values to clear
+inline unsigned prep_grid(int64_t S, int64_t n) {
+    const int64_t a = (S + 255) / 256, b = (n / 8 + 255) / 256, g = a > b ? a : b;
+    return (unsigned)(g < 2048 ? g : 2048);
+}
 
 // number of workgroups for a row-wise grouped GEMM (upper bound on tiles)
 inline unsigned slot_grid(int64_t S, int E, int BM, int NT) {
@@ -848,12 +866,9 @@ hipError_t ffn_fwd_act(const FfnArgs& a, hipStream_t st) {
     if (a.scatter) {   // y = 0, then every slot row times its gate added into y
         float* gs = reinterpret_cast<float*>(
             static_cast<char*>(a.ws) + (a.h_on_load ? 0 : align256((size_t)S * a.f * sizeof(bf16_t))));
-        hipLaunchKernelGGL(fwd_slot_gates, grid1d(S, 256), dim3(256), 0, st, a.gates, a.tim,
-                           S, gs);
-        probe::mark("fwd_slot_gates", st);
-        hipLaunchKernelGGL(zero_bf16, grid1d(a.T * a.d / 8, 256), dim3(256), 0, st,
-                           static_cast<bf16_t*>(a.y), a.T * a.d);
-        probe::mark("zero_bf16", st);
+        hipLaunchKernelGGL(fwd_prep, dim3(prep_grid(S, a.T * a.d)), dim3(256), 0, st, a.gates, a.tim,
+                           S, gs, static_cast<bf16_t*>(a.y), a.T * a.d);
+        probe::mark("fwd_prep", st);
         return second(0, a.d, (int64_t)a.d, static_cast<bf16_t*>(a.y), gs);
     }
     // combined: one column strip of O at a time, straight into y
@@ -946,15 +961,13 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
     ExpertRank* rank = reinterpret_cast<ExpertRank*>(
         static_cast<char*>(a.ws) +
         bwd_main_bytes(S, a.d, a.f, a.E, a.y != nullptr && !a.scatter, a.h_on_load));
-    hipLaunchKernelGGL(expert_ranks, dim3(1), dim3(256), 0, st, a.offsets, a.E, rank);
-    probe::mark("expert_ranks", st);
+    hipLaunchKernelGGL(bwd_prep, dim3(1 + (gs ? prep_grid(S, 0) : 0)), dim3(256), 0, st, a.gates,
+                       a.slot_src, a.offsets, a.E, S, rank, gs);
+    probe::mark("bwd_prep", st);
     // non-gated: the second operand of the two-branch kernels is the first again
     const void* Bx = GATED ? a.B : a.A;
     const void* w3x = GATED ? a.w3 : a.w1;
     if (a.h_on_load) {
-        hipLaunchKernelGGL(slot_gates, grid1d(S, 256), dim3(256), 0, st, a.gates,
-                           a.slot_src, a.offsets, a.E, S, gs);
-        probe::mark("slot_gates", st);
         auto run = [&](auto cfg) {
             using C = decltype(cfg);
             hipLaunchKernelGGL((g3h_kernel<ACT, C>), dim3(wgrad_grid(a.E, cdiv(a.f, C::BM), cdiv(a.d, C::BN))),
@@ -1016,8 +1029,8 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
         return hipGetLastError();
     }
     if (a.scatter) {   // every dX_slot row added into dx (cleared first unless accumulating)
-        if (!a.accumulate) {
-            hipLaunchKernelGGL(zero_bf16, grid1d(a.T * a.d / 8, 256), dim3(256), 0, st,
+        if (!a.accumulate) {   // (only now: every read of dy and x is done)
+            hipLaunchKernelGGL(zero_bf16, dim3(prep_grid(0, a.T * a.d)), dim3(256), 0, st,
                                static_cast<bf16_t*>(a.y), a.T * a.d);
             probe::mark("zero_bf16", st);
         }

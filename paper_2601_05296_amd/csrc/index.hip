@@ -209,6 +209,78 @@ tile_rank(const int32_t* __restrict__ ids, int64_t T, int E, int k, int64_t tb, 
     }
 }
 
+// The whole build in one workgroup, for at most 1024 tokens: a lane per token holds
+// its k ids in registers and sets its bit in a 64-bit mask per wave and expert, as
+// in tile_rank. Three dependent launches took 10 to 17 us of kernels and two launch
+// gaps whatever the size.
+constexpr int ONE_THREADS = 1024;
+
+template <int KMAX>   // k <= KMAX
+__global__ void __launch_bounds__(ONE_THREADS)
+index_one(const int32_t* __restrict__ ids, int T, int E, int k, int32_t* __restrict__ counts,
+          int32_t* __restrict__ offsets, int32_t* __restrict__ eti, int32_t* __restrict__ tim,
+          int32_t* __restrict__ slot_src) {
+    constexpr int NW = ONE_THREADS / WAVE;
+    __shared__ unsigned long long mask[NW][256];
+    __shared__ int32_t first[NW][256];    // slot of the wave's first token of an expert
+    __shared__ int32_t part[4];
+    const int t = threadIdx.x, lane = t & (WAVE - 1), wv = t / WAVE;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const int nw = (T + WAVE - 1) / WAVE;  // waves that hold tokens
+    int id[KMAX];
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) id[j] = j < k && t < T ? ids[t * k + j] : -1;
+    for (int w = wv; w < nw; w += NW)
+        for (int e = lane; e < E; e += WAVE) mask[w][e] = 0ull;
+    __syncthreads();
+    unsigned ok = 0;   // bit j: choice j takes a slot (choice_ok)
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) {
+        bool good = (unsigned)id[j] < (unsigned)E;
+#pragma unroll
+        for (int i = 0; i < j; ++i) good = good && id[i] != id[j];
+        if (good) {
+            ok |= 1u << j;
+            atomicOr(&mask[wv][id[j]], 1ull << lane);
+        }
+    }
+    __syncthreads();
+    // a thread per expert: its tokens by wave, then the segments' starts (whole
+    // waves 0..3)
+    int total = 0, inc = 0;
+    if (t < 256) {
+        if (t < E)
+            for (int w = 0; w < nw; ++w) {
+                first[w][t] = total;
+                total += __popcll(mask[w][t]);
+            }
+        inc = wave_incl_scan(total);
+        if (lane == WAVE - 1) part[wv] = inc;
+    }
+    __syncthreads();
+    if (t < E) {
+        int start = inc - total;
+        for (int w = 0; w < wv; ++w) start += part[w];
+        for (int w = 0; w < nw; ++w) first[w][t] += start;
+        counts[t] = total;
+        offsets[t] = start;
+        if (t == E - 1) offsets[E] = start + total;
+    }
+    __syncthreads();
+    if (t >= T) return;
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) {
+        if (j >= k) break;
+        int r = -1;
+        if ((ok >> j) & 1u) {
+            r = first[wv][id[j]] + __popcll(mask[wv][id[j]] & below);
+            eti[r] = t;
+            slot_src[r] = t * k + j;
+        }
+        tim[t * k + j] = r;
+    }
+}
+
 }  // namespace
 
 // Device address of `scratch` on the current device, looked up once per
@@ -246,6 +318,13 @@ size_t build_index_workspace(int64_t T, int E, int k) {
 hipError_t build_index(const int32_t* ids, int64_t T, int E, int k, int32_t* counts,
                        int32_t* offsets, int32_t* eti, int32_t* tim, int32_t* slot_src,
                        void* ws, hipStream_t st) {
+    if (T <= ONE_THREADS) {
+        auto kernel = k <= 4 ? index_one<4> : k <= 8 ? index_one<8> : index_one<16>;
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(ONE_THREADS), 0, st, ids, (int)T, E, k, counts,
+                           offsets, eti, tim, slot_src);
+        probe::mark("index_one", st);
+        return hipGetLastError();
+    }
     const int64_t tb = tile_tokens(T);
     const int ntiles = (int)((T + tb - 1) / tb);
     int32_t* cnt = static_cast<int32_t*>(ws);

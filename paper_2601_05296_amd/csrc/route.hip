@@ -224,6 +224,115 @@ route_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg,
     }
 }
 
+// Few tokens, in two launches. One workgroup that reads all of W_g gets some 25 GB/s
+// of it (64 experts x 2048: 256 KB, 13 us for a single token), and a short grid has
+// no others to share the reading with; so the product is split over blocks of 16
+// experts as well, through the logits output, and softmax and top-k follow.
+
+// logits[t][e] = x[t] . W_g[e] + bias[e]: 16 tokens x 16 experts per workgroup, its
+// eight waves each take an eighth of K straight from global memory into the MFMA
+// operands, eight steps in flight; the partial sums meet in LDS in wave order.
+constexpr int RL_WAVES = 8;
+__global__ void __launch_bounds__(RL_WAVES * WAVE)
+route_logits(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg,
+             const float* __restrict__ bias, int64_t T, int d, int E, float* __restrict__ logits) {
+    __shared__ float part[RL_WAVES][16][17];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int col = lane & 15, grp = lane >> 4;
+    const int64_t t0 = (int64_t)blockIdx.x * 16;
+    const int e0 = blockIdx.y * 16;
+    const int n = d / 32, s0 = wv * n / RL_WAVES, s1 = (wv + 1) * n / RL_WAVES;
+    const bf16_t* xr = x + (t0 + col < T ? t0 + col : T - 1) * d + grp * 8;
+    const bf16_t* wr = wg + (int64_t)min(e0 + col, E - 1) * d + grp * 8;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    constexpr int U = 8;
+    for (int s = s0; s < s1; s += U) {
+        bf16x8 q[U], p[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int o = min(s + u, s1 - 1) * 32;
+            q[u] = *reinterpret_cast<const bf16x8*>(xr + o);
+            p[u] = *reinterpret_cast<const bf16x8*>(wr + o);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s + u < s1) acc = mfma16x16x32(p[u], q[u], acc);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wv][col][grp * 4 + r] = acc[r];   // token col, expert 4 grp + r
+    __syncthreads();
+    if (threadIdx.x >= 256) return;
+    const int tok = threadIdx.x >> 4, e = e0 + (threadIdx.x & 15);
+    float v = part[0][tok][threadIdx.x & 15];
+#pragma unroll
+    for (int w = 1; w < RL_WAVES; ++w) v += part[w][tok][threadIdx.x & 15];
+    if (e >= E || t0 + tok >= T) return;
+    if (bias) v += bias[e];
+    logits[(t0 + tok) * E + e] = v;
+}
+
+// Softmax and top-k of given logits, one wave per token. An expert's place is the
+// number of experts that come before it: larger logits, and equal ones of lower ids.
+// Counting them against the row in LDS (broadcast reads) takes no chain of
+// cross-lane exchanges, of which k rounds of argmax take 12 each. A NaN comes before
+// nothing and has no place; places without an expert keep id 0x7fffffff.
+constexpr int RP_TOK = 4;
+__global__ void __launch_bounds__(RP_TOK * WAVE)
+route_pick(const float* __restrict__ logits, int64_t T, int E, int k, int renorm,
+           int32_t* __restrict__ ids, float* __restrict__ gates) {
+    __shared__ __align__(16) float row[RP_TOK][256];
+    __shared__ float selv[RP_TOK][16];
+    __shared__ int sele[RP_TOK][16];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t t = (int64_t)blockIdx.x * RP_TOK + w;
+    const bool valid = t < T;
+    float* l = row[w];
+    float mx = -INFINITY, z = 0.f;
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = lane + i * WAVE;
+        v[i] = valid && e < E ? logits[t * E + e] : -INFINITY;
+        l[e] = v[i];
+        if (e < E) mx = fmaxf(mx, v[i]);
+    }
+    if (lane < 16) { selv[w][lane] = -INFINITY; sele[w][lane] = 0x7fffffff; }
+    mx = wave_max(mx);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (lane + i * WAVE < E) z += __expf(v[i] - mx);
+    z = wave_sum(z);
+    __syncthreads();
+    // (entries E .. 255 of the row are -infinity and come before nothing)
+    int place[4] = {0, 0, 0, 0};
+    for (int o = 0; o < E; o += 4) {
+        const f32x4 u = *reinterpret_cast<const f32x4*>(l + o);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i * WAVE >= E) break;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                place[i] += (u[r] > v[i]) | ((u[r] == v[i]) & (o + r < lane + i * WAVE));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = lane + i * WAVE;
+        if (e < E && v[i] == v[i] && place[i] < k) { selv[w][place[i]] = v[i]; sele[w][place[i]] = e; }
+    }
+    __syncthreads();
+    if (lane < k && valid) {
+        const float pe = __expf(selv[w][lane] - mx);
+        float sum = z;
+        if (renorm) {
+            sum = 0.f;
+            for (int j = 0; j < k; ++j) sum += __expf(selv[w][j] - mx);
+        }
+        ids[t * k + lane] = sele[w][lane];
+        gates[t * k + lane] = pe / sum;
+    }
+}
+
 // f32: 16 tokens per workgroup. The product runs on v_mfma_f32_16x16x4_f32
 // straight from global memory, each of the four waves taking a quarter of K for
 // all experts; the partial logits meet in LDS, and 16 lanes per token then take
@@ -371,6 +480,20 @@ hipError_t route(const void* x, const void* wg, const float* bias, int64_t T, in
                            static_cast<const float*>(wg), bias, T, d, E, k, (int)renorm, ids,
                            gates, logits);
         probe::mark("route_f32", st);
+        return hipGetLastError();
+    }
+    // Two launches where W_g is large (from 128 KB on) and the tokens are few. Kernel
+    // times in us, one launch and two: E = 64, d = 2048: T = 1 (16, 10), 1021 (17, 12),
+    // 4000 (17, 25); E = 128, d = 2880: T = 300 (32, 18), 2000 (33, 43); E = 4, d =
+    // 512: T = 700 (4, 9).
+    if (logits && (int64_t)E * d >= 65536 && T * E <= 98304) {
+        hipLaunchKernelGGL(route_logits, dim3((unsigned)((T + 15) / 16), (unsigned)((E + 15) / 16)),
+                           dim3(RL_WAVES * WAVE), 0, st, static_cast<const bf16_t*>(x),
+                           static_cast<const bf16_t*>(wg), bias, T, d, E, logits);
+        probe::mark("route_logits", st);
+        hipLaunchKernelGGL(route_pick, dim3((unsigned)((T + RP_TOK - 1) / RP_TOK)), dim3(RP_TOK * WAVE), 0,
+                           st, logits, T, E, k, (int)renorm, ids, gates);
+        probe::mark("route_pick", st);
         return hipGetLastError();
     }
     if (E <= 32) return launch_route_bf16<2>(x, wg, bias, T, d, E, k, renorm, ids, gates, logits, st);

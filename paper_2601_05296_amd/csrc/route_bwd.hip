@@ -161,6 +161,7 @@ __global__ void rb_dwg_reduce(const float* __restrict__ part, int nsplit, int E,
 }
 
 using CR = rs::Cfg<256, 256, 2, 4, 1>;
+using CRN = rs::Cfg<128, 128, 2, 2, 1>;
 constexpr int RB_MCH = 512;  // least tokens per split of the MFMA dW_g kernel
 
 inline int epad(int E) { return (E + 31) / 32 * 32; }
@@ -219,14 +220,14 @@ rb_dlogits_hilo(const float* __restrict__ dg, const float* __restrict__ logits,
     }
 }
 
-// dx[t] (+)= sum_k hl[t][k] * W_g[k mod Ep]   (tile: 256 tokens x 256 columns)
-__global__ void __launch_bounds__(CR::THREADS)
-rb_dx_mfma(const bf16_t* __restrict__ hl, const bf16_t* __restrict__ wg, int64_t T, int d,
-           int E, int Ep, int accumulate, bf16_t* __restrict__ dx) {
-    extern __shared__ __align__(16) char lds[];
-    using C = CR;
-    const int64_t m0 = (int64_t)blockIdx.x * C::BM;
-    const int n0 = blockIdx.y * C::BN;
+// dx[t] (+)= sum_k hl[t][k] * W_g[k mod Ep]   (tile: BM tokens x BN columns)
+template <class C>
+__device__ __forceinline__ void rb_dx_tile(int mt, int nt, const bf16_t* __restrict__ hl,
+                                           const bf16_t* __restrict__ wg, int64_t T, int d, int E,
+                                           int Ep, int accumulate, bf16_t* __restrict__ dx,
+                                           char* lds) {
+    const int64_t m0 = (int64_t)mt * C::BM;
+    const int n0 = nt * C::BN;
     const int rows = (int)min((int64_t)C::BM, T - m0);
     rs::DenseKC2<C, C::BM> la;
     la.init(hl, hl, 2 * Ep, m0, rows, 2 * Ep);
@@ -279,14 +280,12 @@ rb_dx_mfma(const bf16_t* __restrict__ hl, const bf16_t* __restrict__ wg, int64_t
 }
 
 // part[split][m][n] = sum over the split's tokens of hl[t][m] * x[t][n], m < 2Ep
-__global__ void __launch_bounds__(CR::THREADS)
-rb_dwg_mfma(const bf16_t* __restrict__ hl, const bf16_t* __restrict__ x, int64_t T, int d,
-            int Ep, int64_t chunk, float* __restrict__ part) {
-    extern __shared__ __align__(16) char lds[];
-    using C = CR;
-    const int n0 = blockIdx.x * C::BN;
-    const int m0 = blockIdx.y * C::BM;
-    const int split = blockIdx.z;
+template <class C>
+__device__ __forceinline__ void rb_dwg_tile(int nt, int mt, int split, const bf16_t* __restrict__ hl,
+                                            const bf16_t* __restrict__ x, int64_t T, int d, int Ep,
+                                            int64_t chunk, float* __restrict__ part, char* lds) {
+    const int n0 = nt * C::BN;
+    const int m0 = mt * C::BM;
     const int64_t t0 = (int64_t)split * chunk;
     const int cnt = (int)min(chunk, T - t0);
     const int M = 2 * Ep;
@@ -316,6 +315,26 @@ rb_dwg_mfma(const bf16_t* __restrict__ hl, const bf16_t* __restrict__ x, int64_t
     }
 }
 
+// Both products of the router backward in one launch: the first n_dx workgroups
+// take dx tiles (bound by reading and writing dx), the others dW_g tiles (by
+// reading x), so that neither waits for the other's last wave.
+template <class C>
+__global__ void __launch_bounds__(C::THREADS, 2)
+rb_products(const bf16_t* __restrict__ hl, const bf16_t* __restrict__ wg,
+            const bf16_t* __restrict__ x, int64_t T, int d, int E, int Ep, int accumulate,
+            int n_dx, int64_t chunk, bf16_t* __restrict__ dx, float* __restrict__ part) {
+    extern __shared__ __align__(16) char lds[];
+    const int NT = (d + C::BN - 1) / C::BN;
+    int b = blockIdx.x;
+    if (b < n_dx) {
+        rb_dx_tile<C>(b / NT, b % NT, hl, wg, T, d, E, Ep, accumulate, dx, lds);
+        return;
+    }
+    b -= n_dx;
+    const int MT = (2 * Ep + C::BM - 1) / C::BM;
+    rb_dwg_tile<C>(b % NT, b / NT % MT, b / (NT * MT), hl, x, T, d, Ep, chunk, part, lds);
+}
+
 // dw_gate[e][i] = sum_split (part[split][e][i] + part[split][Ep + e][i])
 __global__ void rb_dwg_reduce_hilo(const float* __restrict__ part, int nsplit, int E, int Ep,
                                    int d, float* __restrict__ dwg) {
@@ -341,16 +360,25 @@ inline int nsplits(int64_t T) { const int64_t c = split_tokens(T, RB_CHUNK); ret
 inline int msplits(int64_t T) { const int64_t c = split_tokens(T, RB_MCH); return (int)((T + c - 1) / c); }
 inline size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 
-hipError_t set_rb_lds_limits() {
-    static hipError_t status = [] {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(rb_dx_mfma),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, CR::LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(rb_dwg_mfma),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, CR::LDS);
-        return e;
-    }();
-    return status;
+template <class C>
+inline int64_t rb_dx_tiles(int64_t T, int d) { return (T + C::BM - 1) / C::BM * ((d + C::BN - 1) / C::BN); }
+template <class C>
+inline int64_t rb_dwg_tiles(int d, int Ep, int splits) {
+    return (int64_t)((d + C::BN - 1) / C::BN) * ((2 * Ep + C::BM - 1) / C::BM) * splits;
+}
+
+template <class C>
+hipError_t launch_products(const bf16_t* hl, const void* wg, const void* x, int64_t T, int d, int E,
+                           int Ep, bool accumulate, void* dx, float* part, hipStream_t st) {
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(rb_products<C>), hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+    if (attr != hipSuccess) return attr;
+    const int64_t n_dx = rb_dx_tiles<C>(T, d), n_dwg = rb_dwg_tiles<C>(d, Ep, msplits(T));
+    hipLaunchKernelGGL(rb_products<C>, dim3((unsigned)(n_dx + n_dwg)), dim3(C::THREADS), C::LDS, st, hl,
+                       (const bf16_t*)wg, (const bf16_t*)x, T, d, E, Ep, (int)accumulate, (int)n_dx,
+                       split_tokens(T, RB_MCH), (bf16_t*)dx, part);
+    probe::mark("rb_products", st);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -391,7 +419,6 @@ hipError_t route_bwd(const float* dgates, const float* logits, const int32_t* id
         probe::mark("rb_dwg_reduce", st);
         return hipGetLastError();
     }
-    if (hipError_t e = set_rb_lds_limits(); e != hipSuccess) return e;
     const int Ep = epad(E);
     bf16_t* hl = static_cast<bf16_t*>(ws);
     float* part = reinterpret_cast<float*>(static_cast<char*>(ws) +
@@ -399,15 +426,14 @@ hipError_t route_bwd(const float* dgates, const float* logits, const int32_t* id
     hipLaunchKernelGGL(rb_dlogits_hilo, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, st, dgates,
                        logits, ids, gates, T, E, Ep, k, (int)renorm, hl);
     probe::mark("rb_dlogits", st);
-    hipLaunchKernelGGL(rb_dx_mfma, dim3((unsigned)((T + CR::BM - 1) / CR::BM), (unsigned)((d + CR::BN - 1) / CR::BN)),
-                       dim3(CR::THREADS), CR::LDS, st, (const bf16_t*)hl, (const bf16_t*)wg, T, d, E,
-                       Ep, (int)accumulate, (bf16_t*)dx);
-    probe::mark("rb_dx", st);
+    // Quarter tiles, two workgroups per CU, where the 256 x 256 ones would leave CUs
+    // idle (T = 1021, d = 2048, E = 64: 48 tiles).
     const int ms = msplits(T);
-    hipLaunchKernelGGL(rb_dwg_mfma, dim3((unsigned)((d + CR::BN - 1) / CR::BN), (unsigned)((2 * Ep + CR::BM - 1) / CR::BM), (unsigned)ms),
-                       dim3(CR::THREADS), CR::LDS, st, (const bf16_t*)hl, (const bf16_t*)x, T, d, Ep,
-                       split_tokens(T, RB_MCH), part);
-    probe::mark("rb_dwg_partial", st);
+    const bool few = rb_dx_tiles<CR>(T, d) + rb_dwg_tiles<CR>(d, Ep, ms) <= 256;
+    if (hipError_t e = few ? launch_products<CRN>(hl, wg, x, T, d, E, Ep, accumulate, dx, part, st)
+                           : launch_products<CR>(hl, wg, x, T, d, E, Ep, accumulate, dx, part, st);
+        e != hipSuccess)
+        return e;
     hipLaunchKernelGGL(rb_dwg_reduce_hilo, dim3((unsigned)(((int64_t)E * d + 255) / 256)), dim3(256), 0,
                        st, part, ms, E, Ep, d, dwg);
     probe::mark("rb_dwg_reduce", st);

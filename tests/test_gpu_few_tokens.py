@@ -1,0 +1,94 @@
+"""Kernels that serve few tokens: the router split over experts (E * d >= 65536),
+the one-workgroup index build (T <= 1024), the combine with a workgroup per token,
+and the router backward in quarter tiles."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2601_05296_amd import binding as B
+from paper_2601_05296_amd import synth
+from tests.parity import assert_close, dev, host, near_tie_ok
+
+pytestmark = pytest.mark.gpu
+
+
+def _bf16(rng, shape, std):
+    s = synth.bf16_round(rng.standard_normal(shape, dtype=np.float32) * np.float32(std))
+    return s, synth.bf16_to_f32(s)
+
+
+def _route(xs, ws, bias, T, d, E, k, renorm):
+    ids = torch.empty((T, k), dtype=torch.int32, device="cuda")
+    gates = torch.empty((T, k), dtype=torch.float32, device="cuda")
+    logits = torch.empty((T, E), dtype=torch.float32, device="cuda")
+    B.moe_route(dev(xs), dev(ws), dev(bias), T, d, E, k, B.MOE_RENORM if renorm else 0, ids, gates,
+                logits)
+    torch.cuda.synchronize()
+    return ids.cpu().numpy(), host(gates), host(logits)
+
+
+# both sides of the split's bounds (E * d >= 65536, T * E <= 98304), ragged token and
+# expert blocks, K shares of one to several steps
+@pytest.mark.parametrize("T,d,E,k,renorm", [
+    (1, 1024, 64, 6, True), (17, 4096, 16, 16, False), (100, 1984, 33, 3, False),
+    (384, 256, 256, 16, True), (385, 256, 256, 16, True), (50, 320, 205, 8, False),
+    (50, 320, 204, 8, False)])
+def test_route_few_tokens(T, d, E, k, renorm):
+    rng = np.random.Generator(np.random.PCG64(T + E))
+    xs, x = _bf16(rng, (T, d), 1.0)
+    ws, wg = _bf16(rng, (E, d), 0.02)
+    bias = rng.standard_normal(E, dtype=np.float32)
+    bias[rng.integers(E)] = -np.inf
+    ids_r, gates_r, logits_r, _ = oracle.route(x, wg, bias, k, renorm)
+    ids, gates, logits = _route(xs, ws, bias, T, d, E, k, renorm)
+    fin = np.isfinite(logits_r)
+    assert np.array_equal(np.isfinite(logits), fin)
+    assert_close("logits", logits[fin], logits_r[fin], "f32")
+    assert near_tie_ok(ids, ids_r, np.where(fin, logits_r, -1e30)) <= 1
+    same = np.all(ids == ids_r, axis=1)
+    assert_close("gates", gates[same], gates_r[same], "f32")
+
+
+def test_route_few_tokens_ties_and_nan():
+    """Equal logits go to the lower id; NaN logits are never chosen (as in the
+    one-launch router), and places without an expert get an id that the index
+    build rejects."""
+    E, k, T, d = 130, 4, 40, 512
+    x = np.zeros((T, d), dtype=np.uint16)
+    x[3] = 0x7FC0                                   # token 3: every logit NaN
+    ws = np.zeros((E, d), dtype=np.uint16)
+    bias = np.zeros(E, dtype=np.float32)
+    bias[[7, 129]] = 1.0
+    bias[[0, 5]] = np.nan
+    ids, _, _ = _route(x, ws, bias, T, d, E, k, False)
+    for t in range(T):
+        if t == 3:
+            assert np.all(ids[t] == 0x7FFFFFFF)
+        else:
+            assert ids[t].tolist() == [7, 129, 1, 2]
+
+
+@pytest.mark.parametrize("T,E,k", [(1, 1, 1), (63, 5, 4), (64, 256, 16), (65, 64, 5), (1023, 128, 8),
+                                   (1024, 200, 9), (1025, 200, 9)])
+def test_index_one_workgroup(T, E, k):
+    rng = np.random.Generator(np.random.PCG64(T))
+    ids = synth.random_ids(T, E, k, seed=T)
+    bad = rng.random(ids.shape) < 0.1               # rejected: out of range or a repeat
+    ids[bad] = rng.choice([-1, E, 0x7FFFFFFF, 0], size=int(bad.sum()))
+    rej = np.zeros(ids.shape, bool)
+    for j in range(k):
+        e = ids[:, j:j + 1]
+        rej[:, j] = ((e < 0) | (e >= E))[:, 0] | (ids[:, :j] == e).any(1)
+    ref = oracle.build_index(np.where(rej, E, ids), E + 1)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    m = [torch.empty(n, **i32) for n in (E, E + 1, T * k, T * k, T * k)]
+    n = B.moe_build_index_workspace_size(T, E, k)
+    ws = torch.empty(max(n, 16), dtype=torch.uint8, device="cuda")
+    B.moe_build_index(dev(ids), T, E, k, *m, ws, n)
+    torch.cuda.synchronize()
+    counts, offsets, eti, tim, ss = (t.cpu().numpy() for t in m)
+    f = int(ref.offsets[E])
+    assert np.array_equal(counts, ref.counts[:E]) and np.array_equal(offsets, ref.offsets[:E + 1])
+    assert np.array_equal(eti[:f], ref.eti[:f]) and np.array_equal(ss[:f], ref.slot_src[:f])
+    assert np.array_equal(tim.reshape(T, k), np.where(rej, -1, ref.tim))
