@@ -9,6 +9,7 @@ is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -100,8 +101,8 @@ def load_library(path: str = LIB):
 
 
 def _ptr(t):
-    if t is None:
-        return None
+    if t is None or t.__class__ is int:
+        return t
     if isinstance(t, int):
         return t
     if not t.is_cuda:
@@ -169,8 +170,16 @@ def _ffn_grads(flags, T, d, f, E, k, dy, gates, slot_src, dw1, dw3, dw2, d_gates
     _need(d_gates, T * k, "d_gates", f32)
 
 
+# torch's current stream as a raw handle. The handle alone, where torch offers it,
+# costs a tenth of building a torch.cuda.Stream around it (0.2 against 2.3 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and _device is not None:
+            return _raw_stream(_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 
@@ -199,6 +208,9 @@ def moe_route(x, w_gate, bias, T, d, E, k, flags, topk_ids, gates, logits, strea
                                     _ptr(topk_ids), _ptr(gates), _ptr(logits), _stream(stream)))
 
 
+# The workspace queries are functions of the sizes alone: their answers are kept
+# (a ctypes call takes about 1 us).
+@functools.lru_cache(maxsize=256, typed=True)
 def moe_build_index_workspace_size(T, E, k) -> int:
     return load_library().moe_build_index_workspace_size(T, E, k)
 
@@ -234,6 +246,7 @@ def moe_build_index_noalloc(topk_ids, T, E, k, counts, offsets, expert_token_ind
                                                   _stream(stream)))
 
 
+@functools.lru_cache(maxsize=256, typed=True)
 def moe_ffn_fwd_workspace_size(T, d, f, E, k, flags) -> int:
     return load_library().moe_ffn_fwd_workspace_size(T, d, f, E, k, flags)
 
@@ -259,6 +272,7 @@ def moe_ffn_recompute(x, w1, w3, offsets, expert_token_indices, T, d, f, E, k, f
                                             _ptr(A), _ptr(B), _stream(stream)))
 
 
+@functools.lru_cache(maxsize=256, typed=True)
 def moe_ffn_fwd_combine_workspace_size(T, d, f, E, k, flags) -> int:
     return load_library().moe_ffn_fwd_combine_workspace_size(T, d, f, E, k, flags)
 
@@ -277,6 +291,7 @@ def moe_ffn_fwd_combine(x, w1, w3, w2, offsets, expert_token_indices, gates, tok
         _ptr(workspace), workspace_bytes, _stream(stream)))
 
 
+@functools.lru_cache(maxsize=256, typed=True)
 def moe_ffn_bwd_combine_workspace_size(T, d, f, E, k, flags) -> int:
     return load_library().moe_ffn_bwd_combine_workspace_size(T, d, f, E, k, flags)
 
@@ -306,6 +321,7 @@ def moe_combine(src, weights, token_index_map, T, d, k, flags, out, stream=None)
                                       flags, _ptr(out), _stream(stream)))
 
 
+@functools.lru_cache(maxsize=256, typed=True)
 def moe_ffn_bwd_workspace_size(T, d, f, E, k, flags) -> int:
     return load_library().moe_ffn_bwd_workspace_size(T, d, f, E, k, flags)
 
@@ -326,6 +342,7 @@ def moe_ffn_bwd(dy, x, w1, w3, w2, gates, offsets, expert_token_indices, slot_sr
                                       _stream(stream)))
 
 
+@functools.lru_cache(maxsize=256, typed=True)
 def moe_route_bwd_workspace_size(T, d, E, k, flags) -> int:
     return load_library().moe_route_bwd_workspace_size(T, d, E, k, flags)
 

@@ -216,50 +216,65 @@ def _forward_recompute(x, w_gate, bias, w1, w3, w2, k, renorm, act, h_on_load, c
 
 def _forward(x, w_gate, bias, w1, w3, w2, k, renorm, keep_O, act, separate, h_on_load,
              atomic_combine):
-    stream = None   # torch's current stream, set by forward()
+    """The calls in order on torch's current stream. A forward of a few tokens takes
+    some 45 us on the GPU, so the host path counts: the caller's tensors are checked
+    as binding.py does, what is allocated here is not, and the raw stream is read
+    once."""
     T, d = x.shape
     E, _, f = w1.shape
     dev = x.device
     flags = B.dtype_flag(x)
     S = T * k
-    i32 = dict(dtype=torch.int32, device=dev)
-    f32 = dict(dtype=torch.float32, device=dev)
-    ids = torch.empty((T, k), **i32)
-    gates = torch.empty((T, k), **f32)
-    logits = torch.empty((T, E), **f32)
-    B.moe_route(x, w_gate, bias, T, d, E, k, flags | (B.MOE_RENORM if renorm else 0), ids, gates,
-                logits, stream)
-    counts = torch.empty(E, **i32)
-    offsets = torch.empty(E + 1, **i32)
-    eti = torch.empty(S, **i32)
-    tim = torch.empty((T, k), **i32)
-    slot_src = torch.empty(S, **i32)
-    wsb = B.moe_build_index_workspace_size(T, E, k)
-    ws = torch.empty(max(wsb, 16), dtype=torch.uint8, device=dev)
-    B.moe_build_index(ids, T, E, k, counts, offsets, eti, tim, slot_src, ws, wsb, stream)
-    del ws
     gated = act == "swiglu"
+    w3g = w3 if gated else None
     fflags = flags | B.ACT_FLAG[act] | (B.MOE_H_ON_LOAD if h_on_load else 0)
-    A = torch.empty((S, f), dtype=x.dtype, device=dev)
-    Bm = torch.empty((S, f), dtype=x.dtype, device=dev) if gated else None
-    y = torch.empty((T, d), dtype=x.dtype, device=dev)
+    lib = B.load_library()
+    el, i32, f32, empty = x.dtype, torch.int32, torch.float32, torch.empty
+    B._need(w_gate, E * d, "w_gate", el)
+    B._need(bias, E, "bias", f32)
+    px, pg, pb = B._ptr(x), B._ptr(w_gate), B._ptr(bias)
+    st = B._stream(None)
+    ids = empty((T, k), dtype=i32, device=dev)
+    gates = empty((T, k), dtype=f32, device=dev)
+    logits = empty((T, E), dtype=f32, device=dev)
+    pi, pt = ids.data_ptr(), gates.data_ptr()
+    B._check(lib.moe_route(px, pg, pb, T, d, E, k, flags | (B.MOE_RENORM if renorm else 0), pi, pt,
+                           logits.data_ptr(), st))
+    counts = empty(E, dtype=i32, device=dev)
+    offsets = empty(E + 1, dtype=i32, device=dev)
+    eti = empty(S, dtype=i32, device=dev)
+    tim = empty((T, k), dtype=i32, device=dev)
+    slot_src = empty(S, dtype=i32, device=dev)
+    # one workspace for the index build and, behind it, the FFN call
+    combined = not (separate or keep_O)
+    cflags = fflags | (B.MOE_ATOMIC_COMBINE if atomic_combine else 0)
+    wsi = B.moe_build_index_workspace_size(T, E, k)
+    wsf = (B.moe_ffn_fwd_combine_workspace_size(T, d, f, E, k, cflags) if combined else
+           B.moe_ffn_fwd_workspace_size(T, d, f, E, k, fflags))
+    ws = empty(max(wsi, wsf, 16), dtype=torch.uint8, device=dev)
+    po, pe, pm, pw = offsets.data_ptr(), eti.data_ptr(), tim.data_ptr(), ws.data_ptr()
+    B._check(lib.moe_build_index(pi, T, E, k, counts.data_ptr(), po, pe, pm, slot_src.data_ptr(), pw,
+                                 wsi, st))
+    A = empty((S, f), dtype=el, device=dev)
+    Bm = empty((S, f), dtype=el, device=dev) if gated else None
+    y = empty((T, d), dtype=el, device=dev)
     saved = Saved(T, d, f, E, k, flags, act, renorm, ids, gates, logits, counts, offsets, eti,
                   tim, slot_src, A, Bm, h_on_load, 0, atomic_combine)
-    w3g = w3 if gated else None
-    if not (separate or keep_O):
-        cflags = saved.combine_flags
-        wsb = B.moe_ffn_fwd_combine_workspace_size(T, d, f, E, k, cflags)
-        ws = torch.empty(max(wsb, 16), dtype=torch.uint8, device=dev)
-        B.moe_ffn_fwd_combine(x, w1, w3g, w2, offsets, eti, gates, tim, T, d, f, E, k, cflags, A,
-                              Bm, y, ws, wsb, stream)
-        del ws
+    B._need(w1, E * d * f, "w1", el)
+    if gated:
+        B._need(w3, E * d * f, "w3", el)
+    B._need(w2, E * f * d, "w2", el)
+    p1, p3, p2 = B._ptr(w1), B._ptr(w3g), B._ptr(w2)
+    pa, pbm = A.data_ptr(), Bm.data_ptr() if gated else None
+    if combined:
+        B._check(lib.moe_ffn_fwd_combine(px, p1, p3, p2, po, pe, pt, pm, T, d, f, E, k, cflags, pa,
+                                         pbm, y.data_ptr(), pw, wsf, st))
         return y, saved
-    O = torch.empty((S, d), dtype=x.dtype, device=dev)
-    wsb = B.moe_ffn_fwd_workspace_size(T, d, f, E, k, fflags)
-    ws = torch.empty(max(wsb, 16), dtype=torch.uint8, device=dev)
-    B.moe_ffn_fwd(x, w1, w3g, w2, offsets, eti, T, d, f, E, k, fflags, A, Bm, O, ws, wsb, stream)
+    O = empty((S, d), dtype=el, device=dev)
+    B._check(lib.moe_ffn_fwd(px, p1, p3, p2, po, pe, T, d, f, E, k, fflags, pa, pbm, O.data_ptr(), pw,
+                             wsf, st))
     del ws
-    B.moe_combine(O, gates, tim, T, d, k, flags, y, stream)
+    B.moe_combine(O, gates, tim, T, d, k, flags, y, st)
     if keep_O:
         return y, saved, O
     del O
