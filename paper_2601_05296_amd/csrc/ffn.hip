@@ -376,22 +376,33 @@ g4_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ w2,
 }
 
 // Weight gradients are written once and not read again by this layer:
-// nontemporal stores keep them from displacing the operands in L2. With
-// `add`, the tile is added to what the array holds (gradients of several
-// token chunks).
+// nontemporal stores keep them from displacing the operands in L2. ADD: the tile
+// is added to what the array holds (gradients of several token chunks).
 __device__ __forceinline__ void st_nt(float* p, const f32x4& v) {
     __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
 }
-__device__ __forceinline__ void st_dw(float* p, const f32x4& v, int add) {
-    st_nt(p, add ? v + *reinterpret_cast<const f32x4*>(p) : v);
+// the tile at (m0, n0) of M x N outputs; at(b, m, n): their addresses
+template <class C, int IPR, bool ADD, class F>
+__device__ __forceinline__ void dw_out(const rs::Acc<C>& acc, char* lds, int m0, int n0, int M, int N,
+                                       F&& at) {
+    if (ADD && m0 + C::BM <= M && n0 + C::BN <= N) {
+        RowStage<C, IPR>::add(acc, lds, [&](int b, int r, int c) { return at(b, m0 + r, n0 + c); }, st_nt);
+        return;
+    }
+    RowStage<C, IPR>::run(acc, lds, [&](int b, int r, int c, const f32x4& v) {
+        const int m = m0 + r, n = n0 + c;
+        if (m >= M || n >= N) return;
+        float* p = at(b, m, n);
+        st_nt(p, ADD ? v + *reinterpret_cast<const f32x4*>(p) : v);
+    });
 }
 
 // G3: dW2[e] = sum_s HG[s]^T dY[eti[s]]   (M = f, N = d, K = slots of e)
-template <class C>
+template <class C, bool ADD>
 __global__ void __launch_bounds__(C::THREADS, 2)
 g3_kernel(const bf16_t* __restrict__ HG, const bf16_t* __restrict__ dy,
           const ExpertRank* __restrict__ rank, const int32_t* __restrict__ eti, int d, int f,
-          int add, float* __restrict__ dw2) {
+          float* __restrict__ dw2) {
     extern __shared__ __align__(16) char lds[];
     const int MT = (f + C::BM - 1) / C::BM, NT = (d + C::BN - 1) / C::BN;
     ExpertRank er;
@@ -410,10 +421,7 @@ g3_kernel(const bf16_t* __restrict__ HG, const bf16_t* __restrict__ dy,
     rs::Acc<C> acc;
     rs::mainloop<C>(la, lb, nl, rs::slices(cnt), lds, acc);
     float* out = dw2 + (int64_t)e * f * d;
-    RowStage<C, 1>::run(acc, lds, [&](int, int r, int c, const f32x4& v) {
-        const int m = m0 + r, n = n0 + c;
-        if (m < f && n < d) st_dw(out + (int64_t)m * d + n, v, add);
-    });
+    dw_out<C, 1, ADD>(acc, lds, m0, n0, f, d, [&](int, int m, int n) { return out + (int64_t)m * d + n; });
 }
 
 
@@ -533,12 +541,12 @@ bwd_prep(const float* __restrict__ gates, const int32_t* __restrict__ slot_src,
 // G3 with g*h formed on load from the saved A (and B) and the slot-ordered
 // gates gs: dW2[e] = sum_s (g h)[s]^T dY[eti[s]]. Runs before G4, which then
 // writes dA, dB over A, B and no g*h.
-template <int ACT, class C>
+template <int ACT, class C, bool ADD>
 __global__ void __launch_bounds__(C::THREADS)
 g3h_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
            const float* __restrict__ gs, const bf16_t* __restrict__ dy,
            const ExpertRank* __restrict__ rank, const int32_t* __restrict__ eti, int d, int f,
-           int add, float* __restrict__ dw2) {
+           float* __restrict__ dw2) {
     extern __shared__ __align__(16) char lds[];
     const int MT = (f + C::BM - 1) / C::BM, NT = (d + C::BN - 1) / C::BN;
     ExpertRank er;
@@ -557,19 +565,16 @@ g3h_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
     rs::Acc<C> acc;
     rs::mainloop<C>(la, lb, nl, rs::slices(cnt), lds, acc);
     float* out = dw2 + (int64_t)e * f * d;
-    RowStage<C, 1>::run(acc, lds, [&](int, int r, int c, const f32x4& v) {
-        const int m = m0 + r, n = n0 + c;
-        if (m < f && n < d) st_dw(out + (int64_t)m * d + n, v, add);
-    });
+    dw_out<C, 1, ADD>(acc, lds, m0, n0, f, d, [&](int, int m, int n) { return out + (int64_t)m * d + n; });
 }
 
 // G5: dW1[e] = x[eti]^T dA, dW3[e] = x[eti]^T dB   (M = d, N = f, K = slots of e)
 // (non-gated: dW1 alone)
-template <int ACT, class C>
+template <int ACT, class C, bool ADD>
 __global__ void __launch_bounds__(C::THREADS, 2)
 g5_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dA,
           const bf16_t* __restrict__ dB, const ExpertRank* __restrict__ rank,
-          const int32_t* __restrict__ eti, int d, int f, int add, float* __restrict__ dw1,
+          const int32_t* __restrict__ eti, int d, int f, float* __restrict__ dw1,
           float* __restrict__ dw3) {
     extern __shared__ __align__(16) char lds[];
     const int MT = (d + C::BM - 1) / C::BM, NT = (f + C::BN - 1) / C::BN;
@@ -591,9 +596,8 @@ g5_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dA,
     rs::mainloop<C>(la, lb0, lb1, rs::slices(cnt), lds, acc);
     float* o1 = dw1 + (int64_t)e * d * f;
     float* o3 = ACT == ACT_SWIGLU ? dw3 + (int64_t)e * d * f : o1;  // dw3 is NULL when non-gated
-    RowStage<C, ACT == ACT_SWIGLU ? 2 : 1>::run(acc, lds, [&](int b, int r, int c, const f32x4& v) {
-        const int m = m0 + r, n = n0 + c;
-        if (m < d && n < f) st_dw((b ? o3 : o1) + (int64_t)m * f + n, v, add);
+    dw_out<C, ACT == ACT_SWIGLU ? 2 : 1, ADD>(acc, lds, m0, n0, d, f, [&](int b, int m, int n) {
+        return (b ? o3 : o1) + (int64_t)m * f + n;
     });
 }
 
@@ -744,22 +748,28 @@ hipError_t set_lds_limits() {
             set(reinterpret_cast<const void*>(g1_kernel<ACT>), CFirst<ACT>::LDS);
             set(reinterpret_cast<const void*>(g4_kernel<ACT, true>), RS::LDS);
             set(reinterpret_cast<const void*>(g4_kernel<ACT, false>), RS::LDS);
-            set(reinterpret_cast<const void*>(g5_kernel<ACT, CFirst<ACT>>), CFirst<ACT>::LDS);
-            set(reinterpret_cast<const void*>(g5_kernel<ACT, CNarrow<ACT>>), CNarrow<ACT>::LDS);
+            set(reinterpret_cast<const void*>(g5_kernel<ACT, CFirst<ACT>, false>), CFirst<ACT>::LDS);
+            set(reinterpret_cast<const void*>(g5_kernel<ACT, CFirst<ACT>, true>), CFirst<ACT>::LDS);
+            set(reinterpret_cast<const void*>(g5_kernel<ACT, CNarrow<ACT>, false>), CNarrow<ACT>::LDS);
+            set(reinterpret_cast<const void*>(g5_kernel<ACT, CNarrow<ACT>, true>), CNarrow<ACT>::LDS);
             set(reinterpret_cast<const void*>(g2h_kernel<ACT, false, RHW>), RHW::LDS);
             set(reinterpret_cast<const void*>(g2h_kernel<ACT, true, RHW>), RHW::LDS);
             set(reinterpret_cast<const void*>(g2h_kernel<ACT, false, RHN>), RHN::LDS);
             set(reinterpret_cast<const void*>(g2h_kernel<ACT, true, RHN>), RHN::LDS);
-            set(reinterpret_cast<const void*>(g3h_kernel<ACT, RHW>), RHW::LDS);
-            set(reinterpret_cast<const void*>(g3h_kernel<ACT, RHN>), RHN::LDS);
+            set(reinterpret_cast<const void*>(g3h_kernel<ACT, RHW, false>), RHW::LDS);
+            set(reinterpret_cast<const void*>(g3h_kernel<ACT, RHW, true>), RHW::LDS);
+            set(reinterpret_cast<const void*>(g3h_kernel<ACT, RHN, false>), RHN::LDS);
+            set(reinterpret_cast<const void*>(g3h_kernel<ACT, RHN, true>), RHN::LDS);
         };
         per_act(std::integral_constant<int, ACT_SWIGLU>{});
         per_act(std::integral_constant<int, ACT_SILU>{});
         per_act(std::integral_constant<int, ACT_RELU>{});
         set(reinterpret_cast<const void*>(g2_kernel<false>), RS::LDS);
         set(reinterpret_cast<const void*>(g2_kernel<true>), RS::LDS);
-        set(reinterpret_cast<const void*>(g3_kernel<RS>), RS::LDS);
-        set(reinterpret_cast<const void*>(g3_kernel<RSN>), RSN::LDS);
+        set(reinterpret_cast<const void*>(g3_kernel<RS, false>), RS::LDS);
+        set(reinterpret_cast<const void*>(g3_kernel<RS, true>), RS::LDS);
+        set(reinterpret_cast<const void*>(g3_kernel<RSN, false>), RSN::LDS);
+        set(reinterpret_cast<const void*>(g3_kernel<RSN, true>), RSN::LDS);
         set(reinterpret_cast<const void*>(g6_kernel<false>), RS::LDS);
         set(reinterpret_cast<const void*>(g6_kernel<true>), RS::LDS);
         return e;
@@ -970,10 +980,10 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
     if (a.h_on_load) {
         auto run = [&](auto cfg) {
             using C = decltype(cfg);
-            hipLaunchKernelGGL((g3h_kernel<ACT, C>), dim3(wgrad_grid(a.E, cdiv(a.f, C::BM), cdiv(a.d, C::BN))),
+            auto g3h = a.accumulate_dw ? g3h_kernel<ACT, C, true> : g3h_kernel<ACT, C, false>;
+            hipLaunchKernelGGL(g3h, dim3(wgrad_grid(a.E, cdiv(a.f, C::BM), cdiv(a.d, C::BN))),
                                dim3(C::THREADS), C::LDS, st, (const bf16_t*)a.A, (const bf16_t*)Bx,
-                               (const float*)gs, (const bf16_t*)a.dy, rank, a.eti, a.d, a.f,
-                               (int)a.accumulate_dw, a.dw2);
+                               (const float*)gs, (const bf16_t*)a.dy, rank, a.eti, a.d, a.f, a.dw2);
         };
         if (few_tiles((int64_t)a.E * cdiv(a.f, RHW::BM) * cdiv(a.d, RHW::BN))) run(RHN{});
         else run(RHW{});
@@ -996,10 +1006,10 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
     if (!a.h_on_load) {
         auto run = [&](auto cfg) {
             using C = decltype(cfg);
-            hipLaunchKernelGGL(g3_kernel<C>, dim3(wgrad_grid(a.E, cdiv(a.f, C::BM), cdiv(a.d, C::BN))),
+            auto g3 = a.accumulate_dw ? g3_kernel<C, true> : g3_kernel<C, false>;
+            hipLaunchKernelGGL(g3, dim3(wgrad_grid(a.E, cdiv(a.f, C::BM), cdiv(a.d, C::BN))),
                                dim3(C::THREADS), C::LDS, st, (const bf16_t*)HG,
-                               (const bf16_t*)a.dy, rank, a.eti, a.d, a.f, (int)a.accumulate_dw,
-                               a.dw2);
+                               (const bf16_t*)a.dy, rank, a.eti, a.d, a.f, a.dw2);
         };
         if (few_tiles((int64_t)a.E * cdiv(a.f, RS::BM) * cdiv(a.d, RS::BN))) run(RSN{});
         else run(RS{});
@@ -1007,10 +1017,10 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
     }
     auto dw13 = [&](auto cfg) {
         using C = decltype(cfg);
-        hipLaunchKernelGGL((g5_kernel<ACT, C>), dim3(wgrad_grid(a.E, cdiv(a.d, C::BM), cdiv(a.f, C::BN))),
+        auto g5 = a.accumulate_dw ? g5_kernel<ACT, C, true> : g5_kernel<ACT, C, false>;
+        hipLaunchKernelGGL(g5, dim3(wgrad_grid(a.E, cdiv(a.d, C::BM), cdiv(a.f, C::BN))),
                            dim3(C::THREADS), C::LDS, st, (const bf16_t*)a.x, (const bf16_t*)a.A,
-                           (const bf16_t*)a.B, rank, a.eti, a.d, a.f, (int)a.accumulate_dw, a.dw1,
-                           a.dw3);
+                           (const bf16_t*)a.B, rank, a.eti, a.d, a.f, a.dw1, a.dw3);
     };
     if (S / a.E <= 96 ||
         few_tiles((int64_t)a.E * cdiv(a.d, CFirst<ACT>::BM) * cdiv(a.f, CFirst<ACT>::BN)))

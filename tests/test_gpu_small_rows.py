@@ -115,3 +115,42 @@ def test_small_rows_same_bits(counts, d, f, act, h_on_load, atomic):
         assert torch.isfinite(a.float()).all(), name
         assert torch.equal(a, rep[name][:T]), name
         assert torch.equal(a, rep[name][-T:]), name
+
+
+@pytest.mark.parametrize("E,rows,d,f,act,h_on_load", [
+    # full and partial tiles of the large weight-gradient tiles (more than 128 of
+    # them, more than 96 slots per expert), and of the small ones
+    (40, 100, 512, 1024, "swiglu", True), (40, 100, 576, 960, "silu", False),
+    (3, 150, 576, 640, "swiglu", True), (2, 90, 512, 512, "relu", False)])
+def test_accumulated_weight_gradients(E, rows, d, f, act, h_on_load):
+    """MOE_ACCUMULATE_DW adds the very gradient that the plain call writes: one
+    float32 addition per element."""
+    T, k = E * rows, 1
+    rng = np.random.Generator(np.random.PCG64(E + d))
+    ids = rng.permutation(np.repeat(np.arange(E), rows)).astype(np.int32)[:, None]
+    x, dy = _bf16(rng, (T, d), 1.0), _bf16(rng, (T, d), 1.0)
+    w1, w3, w2 = (_bf16(rng, (E, d, f), d ** -0.5), _bf16(rng, (E, d, f), d ** -0.5),
+                  _bf16(rng, (E, f, d), f ** -0.5))
+    gates = torch.from_numpy(rng.random((T, 1), dtype=np.float32)).cuda()
+    A0, B0 = _bf16(rng, (T, f), 1.0), _bf16(rng, (T, f), 1.0)
+    ix = oracle.build_index(ids, E)
+    off, eti, ss = dev(ix.offsets), dev(ix.eti), dev(ix.slot_src)
+    gated = act == "swiglu"
+    base = [torch.randn(s, device="cuda") for s in ((E, d, f), (E, d, f), (E, f, d))]
+
+    def run(flags, dw):
+        fl = flags | B.ACT_FLAG[act] | (B.MOE_H_ON_LOAD if h_on_load else 0)
+        n = B.moe_ffn_bwd_workspace_size(T, d, f, E, k, fl)
+        ws = torch.empty(max(n, 16), dtype=torch.uint8, device="cuda")
+        dg = torch.empty((T, 1), dtype=torch.float32, device="cuda")
+        dX = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+        B.moe_ffn_bwd(dy, x, w1, w3 if gated else None, w2, gates, off, eti, ss, A0.clone(),
+                      B0.clone() if gated else None, T, d, f, E, k, fl, dw[0],
+                      dw[1] if gated else None, dw[2], dg, dX, ws, n)
+        torch.cuda.synchronize()
+        return dw
+
+    plain = run(0, [torch.full_like(b, float("nan")) for b in base])
+    acc = run(B.MOE_ACCUMULATE_DW, [b.clone() for b in base])
+    for i in (0, 1, 2) if gated else (0, 2):
+        assert torch.equal(acc[i], base[i] + plain[i]), i
