@@ -227,45 +227,71 @@ route_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg,
 // Few tokens, in two launches. One workgroup that reads all of W_g gets some 25 GB/s
 // of it (64 experts x 2048: 256 KB, 13 us for a single token), and a short grid has
 // no others to share the reading with; so the product is split over blocks of 16
-// experts as well, through the logits output, and softmax and top-k follow.
+// experts as well, through the logits output, and softmax and top-k follow. Both
+// launches add up in route_bf16's order, so that a token's routing has the same bits
+// however many tokens it comes with, and whether or not the logits are asked for.
 
-// logits[t][e] = x[t] . W_g[e] + bias[e]: 16 tokens x 16 experts per workgroup, its
-// eight waves each take an eighth of K straight from global memory into the MFMA
-// operands, eight steps in flight; the partial sums meet in LDS in wave order.
+// logits[t][e] = x[t] . W_g[e] + bias[e]: 16 tokens x 16 experts per workgroup. KG
+// groups of waves take a contiguous share of K each, as route_bf16's do. A wave holds
+// the operands of U steps of 32 k in registers, straight from global memory, and the
+// steps of its next round in flight; the accumulator of the group goes from wave to
+// wave in K order through LDS (a chain of 32 MFMAs per group at d = 2048; 0.6 us more
+// than eight shares of K that are summed at the end, at T = 1, E = 64, d = 2048).
 constexpr int RL_WAVES = 8;
+template <int KG>
 __global__ void __launch_bounds__(RL_WAVES * WAVE)
 route_logits(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg,
              const float* __restrict__ bias, int64_t T, int d, int E, float* __restrict__ logits) {
-    __shared__ float part[RL_WAVES][16][17];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int NW = RL_WAVES / KG;   // waves per K group
+    constexpr int U = 8;
+    __shared__ f32x4 sum[KG][WAVE];
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    const int kg = wv / NW, w = wv % NW;
     const int col = lane & 15, grp = lane >> 4;
     const int64_t t0 = (int64_t)blockIdx.x * 16;
     const int e0 = blockIdx.y * 16;
-    const int n = d / 32, s0 = wv * n / RL_WAVES, s1 = (wv + 1) * n / RL_WAVES;
-    const bf16_t* xr = x + (t0 + col < T ? t0 + col : T - 1) * d + grp * 8;
-    const bf16_t* wr = wg + (int64_t)min(e0 + col, E - 1) * d + grp * 8;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    constexpr int U = 8;
-    for (int s = s0; s < s1; s += U) {
-        bf16x8 q[U], p[U];
+    const int n = d / 32 / KG;          // steps per K group
+    const int k0 = kg * n * 32 + grp * 8;
+    const bf16_t* xr = x + (t0 + col < T ? t0 + col : T - 1) * d + k0;
+    const bf16_t* wr = wg + (int64_t)min(e0 + col, E - 1) * d + k0;
+    bf16x8 q[2][U], p[2][U];            // by round parity
+    auto load = [&](auto par, int s) __attribute__((always_inline)) {
+        constexpr int P = decltype(par)::value;
+        if (s >= n) return;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int o = min(s + u, s1 - 1) * 32;
-            q[u] = *reinterpret_cast<const bf16x8*>(xr + o);
-            p[u] = *reinterpret_cast<const bf16x8*>(wr + o);
+            const int o = min(s + u, n - 1) * 32;
+            q[P][u] = *reinterpret_cast<const bf16x8*>(xr + o);
+            p[P][u] = *reinterpret_cast<const bf16x8*>(wr + o);
         }
+    };
+    // steps [s0, s0 + NW * U), U per wave and turn
+    auto round = [&](auto par, int s0) __attribute__((always_inline)) {
+        constexpr int P = decltype(par)::value;
+        const int s = s0 + w * U;
+        load(std::integral_constant<int, P ^ 1>{}, s + NW * U);
+        for (int turn = 0; turn < NW; ++turn) {
+            if (turn == w && s < n) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                if (s > 0) acc = sum[kg][lane];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (s + u < s1) acc = mfma16x16x32(p[u], q[u], acc);
+                for (int u = 0; u < U; ++u)
+                    if (s + u < n) acc = mfma16x16x32(p[P][u], q[P][u], acc);
+                sum[kg][lane] = acc;
+            }
+            lds_barrier();
+        }
+    };
+    load(std::integral_constant<int, 0>{}, w * U);
+    for (int s0 = 0; s0 < n; s0 += 2 * NW * U) {
+        round(std::integral_constant<int, 0>{}, s0);
+        if (s0 + NW * U < n) round(std::integral_constant<int, 1>{}, s0 + NW * U);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) part[wv][col][grp * 4 + r] = acc[r];   // token col, expert 4 grp + r
-    __syncthreads();
     if (threadIdx.x >= 256) return;
-    const int tok = threadIdx.x >> 4, e = e0 + (threadIdx.x & 15);
-    float v = part[0][tok][threadIdx.x & 15];
-#pragma unroll
-    for (int w = 1; w < RL_WAVES; ++w) v += part[w][tok][threadIdx.x & 15];
+    const int tok = threadIdx.x >> 4, ee = threadIdx.x & 15, e = e0 + ee;
+    // lane 16 * (ee / 4) + tok holds expert ee in element ee % 4
+    float v = sum[0][(ee >> 2) * 16 + tok][ee & 3];
+    if constexpr (KG == 2) v += sum[KG - 1][(ee >> 2) * 16 + tok][ee & 3];
     if (e >= E || t0 + tok >= T) return;
     if (bias) v += bias[e];
     logits[(t0 + tok) * E + e] = v;
@@ -281,6 +307,7 @@ __global__ void __launch_bounds__(RP_TOK * WAVE)
 route_pick(const float* __restrict__ logits, int64_t T, int E, int k, int renorm,
            int32_t* __restrict__ ids, float* __restrict__ gates) {
     __shared__ __align__(16) float row[RP_TOK][256];
+    __shared__ __align__(16) float ex[RP_TOK][256];
     __shared__ float selv[RP_TOK][16];
     __shared__ int sele[RP_TOK][16];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -299,10 +326,20 @@ route_pick(const float* __restrict__ logits, int64_t T, int E, int k, int renorm
     if (lane < 16) { selv[w][lane] = -INFINITY; sele[w][lane] = 0x7fffffff; }
     mx = wave_max(mx);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (lane + i * WAVE < E) z += __expf(v[i] - mx);
-    z = wave_sum(z);
+    for (int i = 0; i < 4; ++i) {
+        const int e = lane + i * WAVE;
+        ex[w][e] = e < E ? __expf(v[i] - mx) : 0.f;
+    }
     __syncthreads();
+    // the exponentials add up as in route_bf16: four groups, each over its runs of
+    // four experts, then the groups
+    for (int o = 4 * (lane & 3); o < E; o += 16) {
+        const f32x4 u = *reinterpret_cast<const f32x4*>(ex[w] + o);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z += u[r];
+    }
+    z += __shfl_xor(z, 1, 64);
+    z += __shfl_xor(z, 2, 64);
     // (entries E .. 255 of the row are -infinity and come before nothing)
     int place[4] = {0, 0, 0, 0};
     for (int o = 0; o < E; o += 4) {
@@ -451,6 +488,11 @@ hipError_t launch_route_shape(const void* x, const void* wg, const float* bias, 
     return hipGetLastError();
 }
 
+// K groups of the bf16 router (RtShape)
+inline int k_groups(int64_t T, int d, int E) {
+    return E <= 128 && T < 32768 && (d / RT_BK) % 2 == 0 ? 2 : 1;
+}
+
 template <int NE>
 hipError_t launch_route_bf16(const void* x, const void* wg, const float* bias, int64_t T,
                              int d, int E, int k, bool renorm, int32_t* ids, float* gates,
@@ -461,7 +503,7 @@ hipError_t launch_route_bf16(const void* x, const void* wg, const float* bias, i
                                                   logits, st);
     }
     if constexpr (NE <= 8) {
-        if (T < 32768 && (d / RT_BK) % 2 == 0)
+        if (k_groups(T, d, E) == 2)
             return launch_route_shape<NE, 64, 2>(x, wg, bias, T, d, E, k, renorm, ids, gates,
                                                  logits, st);
     }
@@ -487,7 +529,8 @@ hipError_t route(const void* x, const void* wg, const float* bias, int64_t T, in
     // 4000 (17, 25); E = 128, d = 2880: T = 300 (32, 18), 2000 (33, 43); E = 4, d =
     // 512: T = 700 (4, 9).
     if (logits && (int64_t)E * d >= 65536 && T * E <= 98304) {
-        hipLaunchKernelGGL(route_logits, dim3((unsigned)((T + 15) / 16), (unsigned)((E + 15) / 16)),
+        auto product = k_groups(T, d, E) == 2 ? route_logits<2> : route_logits<1>;
+        hipLaunchKernelGGL(product, dim3((unsigned)((T + 15) / 16), (unsigned)((E + 15) / 16)),
                            dim3(RL_WAVES * WAVE), 0, st, static_cast<const bf16_t*>(x),
                            static_cast<const bf16_t*>(wg), bias, T, d, E, logits);
         probe::mark("route_logits", st);

@@ -2,6 +2,8 @@
 import numpy as np
 import torch
 
+from paper_2601_05296_amd import binding as B
+
 # Tolerance on max|gpu - ref| / max|ref| per tensor: bf16 storage with float32
 # accumulation, and the float32 debug mode.
 TOL = {"bf16": 2e-2, "f32": 1e-4}
@@ -77,3 +79,15 @@ def near_tie_ok(ids_gpu, ids_ref, logits_ref, tol=1e-4):
             a, b = l[ids_gpu[t, j]], l[ids_ref[t, j]]
             assert abs(a - b) <= tol * (1 + abs(b)), (t, j, ids_gpu[t], ids_ref[t], a, b)
     return int(diff.sum())
+
+
+def launched(fn):
+    """Names of the kernels that fn() launches through the library, in order."""
+    B.moe_probe_enable(256)
+    try:
+        fn()
+        torch.cuda.synchronize()
+        assert B.moe_probe_dropped() == 0
+        return [B.moe_probe_get(i)[0] for i in range(B.moe_probe_count())]
+    finally:
+        B.moe_probe_disable()

@@ -1,5 +1,4 @@
-"""Kernels that serve few tokens: the router split over experts (E * d >= 65536),
-the one-workgroup index build (T <= 1024), the combine with a workgroup per token,
+"""Kernels that serve few tokens: the router split over experts, the one-workgroup index build (T <= 1024), the combine with a workgroup per token,
 and the router backward in quarter tiles."""
 import numpy as np
 import pytest
@@ -8,7 +7,7 @@ import torch
 from oracle import oracle
 from paper_2601_05296_amd import binding as B
 from paper_2601_05296_amd import synth
-from tests.parity import assert_close, dev, host, near_tie_ok
+from tests.parity import assert_close, dev, host, launched, near_tie_ok
 
 pytestmark = pytest.mark.gpu
 
@@ -18,14 +17,14 @@ def _bf16(rng, shape, std):
     return s, synth.bf16_to_f32(s)
 
 
-def _route(xs, ws, bias, T, d, E, k, renorm):
+def _route(xs, ws, bias, T, d, E, k, renorm, want_logits=True):
     ids = torch.empty((T, k), dtype=torch.int32, device="cuda")
     gates = torch.empty((T, k), dtype=torch.float32, device="cuda")
-    logits = torch.empty((T, E), dtype=torch.float32, device="cuda")
+    logits = torch.empty((T, E), dtype=torch.float32, device="cuda") if want_logits else None
     B.moe_route(dev(xs), dev(ws), dev(bias), T, d, E, k, B.MOE_RENORM if renorm else 0, ids, gates,
                 logits)
     torch.cuda.synchronize()
-    return ids.cpu().numpy(), host(gates), host(logits)
+    return ids.cpu().numpy(), host(gates), host(logits) if want_logits else None
 
 
 # both sides of the split's bounds (E * d >= 65536, T * E <= 98304), ragged token and
@@ -48,6 +47,36 @@ def test_route_few_tokens(T, d, E, k, renorm):
     assert near_tie_ok(ids, ids_r, np.where(fin, logits_r, -1e30)) <= 1
     same = np.all(ids == ids_r, axis=1)
     assert_close("gates", gates[same], gates_r[same], "f32")
+
+
+# one and two K groups (odd slice counts and E > 128 have one), K shares that end
+# in the middle of a wave's turn and of the last wave's, several rounds of turns
+@pytest.mark.parametrize("T,d,E,k,renorm", [
+    (1, 2048, 64, 6, True), (48, 2048, 64, 6, False), (300, 2880, 128, 4, False),
+    (16, 4096, 16, 16, False), (9, 8320, 8, 2, False), (64, 1024, 200, 9, False),
+    (70, 576, 130, 5, False), (40, 640, 103, 8, True), (21, 4160, 65, 3, False),
+    (1024, 1088, 64, 6, False)])
+def test_route_same_bits_in_one_and_two_launches(T, d, E, k, renorm):
+    """A token's routing does not depend on the launches that compute it: without the
+    logits output (one launch), and among so many tokens that one launch serves
+    them, ids, gates and logits are the same bits."""
+    rng = np.random.Generator(np.random.PCG64(T + d))
+    xs, _ = _bf16(rng, (T, d), 1.0)
+    ws, _ = _bf16(rng, (E, d), 0.02)
+    bias = rng.standard_normal(E, dtype=np.float32)
+    n = 98304 // (T * E) + 1
+    assert n * T < 32768       # beyond, the one-launch router has one K group
+    out = []
+
+    def run(xs, T, want_logits):
+        return launched(lambda: out.append(_route(xs, ws, bias, T, d, E, k, renorm, want_logits)))
+
+    assert run(xs, T, True) == ["route_logits", "route_pick"]
+    assert run(xs, T, False) == ["route_bf16"]
+    assert run(np.tile(xs, (n, 1)), n * T, True) == ["route_bf16"]
+    for a, b, c in zip(*out):
+        assert b is None or np.array_equal(a, b)
+        assert np.array_equal(a, c[:T])
 
 
 def test_route_few_tokens_ties_and_nan():
