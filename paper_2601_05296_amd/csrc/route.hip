@@ -510,6 +510,25 @@ hipError_t launch_route_bf16(const void* x, const void* wg, const float* bias, i
     return launch_route_shape<NE, 64, 1>(x, wg, bias, T, d, E, k, renorm, ids, gates, logits, st);
 }
 
+// Two launches where W_g is large (from 128 KB on) and the tokens are few. Times in us
+// of one launch and of two (T in brackets):
+//  - E = 64, d = 2048: [1] 17.0, 13.8; [1024] 17.4, 16.5; [1536] 17.6, 21.0. E = 48:
+//    [1024] 16.7, 15.8; [1536] 16.8, 20.3. Up to 64 experts, as long as the product's
+//    16 x 16 tiles run in one round of the 256 CUs.
+//  - E = 96, d = 2048: [768] 28.7, 23.5; [1024] 28.8, 23.7; [1536] 28.9, 29.1. E = 128, d =
+//    2880: [300] 35.6, 23; [768] 35.7, 30.2. E = 256, d = 2048: [384] 53, 42.1.
+//  - the second launch's counting grows with E, the product with d: E = 256, d = 256:
+//    [17] 30.2, 34.3; d = 512: [17] 33.0, 33.9, [128] 36.4, 35.0; d = 768: [128] 39.1, 34.9.
+//  - up to 32 experts one launch stages few rows of W_g: E = 16, d = 4096: [1] 16.3,
+//    15.7, [17] 16.5, 18.6; E = 8, d = 8192: [1] 25.0, 19.0, [4096] 26.7, 31.8; E = 32, d =
+//    2048: [1] 12.3, 13.0. A long K and one tile of tokens only.
+inline bool two_launches(int64_t T, int d, int E) {
+    const int64_t tiles = (T + 15) / 16 * ((E + 15) / 16);
+    if (E <= 32) return T <= 16 && d >= 4096 && (int64_t)E * d >= 65536;
+    if ((int64_t)E * d < 65536 || d < 2 * E) return false;
+    return E <= 64 ? tiles <= 256 : T * E <= 98304;
+}
+
 }  // namespace
 
 hipError_t route(const void* x, const void* wg, const float* bias, int64_t T, int d, int E,
@@ -524,11 +543,7 @@ hipError_t route(const void* x, const void* wg, const float* bias, int64_t T, in
         probe::mark("route_f32", st);
         return hipGetLastError();
     }
-    // Two launches where W_g is large (from 128 KB on) and the tokens are few. Kernel
-    // times in us, one launch and two: E = 64, d = 2048: T = 1 (16, 10), 1021 (17, 12),
-    // 4000 (17, 25); E = 128, d = 2880: T = 300 (32, 18), 2000 (33, 43); E = 4, d =
-    // 512: T = 700 (4, 9).
-    if (logits && (int64_t)E * d >= 65536 && T * E <= 98304) {
+    if (logits && two_launches(T, d, E)) {
         auto product = k_groups(T, d, E) == 2 ? route_logits<2> : route_logits<1>;
         hipLaunchKernelGGL(product, dim3((unsigned)((T + 15) / 16), (unsigned)((E + 15) / 16)),
                            dim3(RL_WAVES * WAVE), 0, st, static_cast<const bf16_t*>(x),

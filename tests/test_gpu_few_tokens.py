@@ -27,12 +27,15 @@ def _route(xs, ws, bias, T, d, E, k, renorm, want_logits=True):
     return ids.cpu().numpy(), host(gates), host(logits) if want_logits else None
 
 
-# both sides of the split's bounds (E * d >= 65536, T * E <= 98304), ragged token and
-# expert blocks, K shares of one to several steps
+# both sides of the split's bounds (E * d >= 65536, d >= 2 E; 16 tokens up to 32
+# experts, 256 tiles up to 64, T * E <= 98304 beyond), ragged token and expert blocks,
+# K shares of one to several steps
 @pytest.mark.parametrize("T,d,E,k,renorm", [
     (1, 1024, 64, 6, True), (17, 4096, 16, 16, False), (100, 1984, 33, 3, False),
     (384, 256, 256, 16, True), (385, 256, 256, 16, True), (50, 320, 205, 8, False),
-    (50, 320, 204, 8, False)])
+    (50, 320, 204, 8, False), (50, 512, 256, 16, False), (16, 4096, 16, 2, False),
+    (1360, 2048, 33, 5, True), (1361, 2048, 33, 5, True), (768, 768, 128, 8, True),
+    (769, 768, 128, 8, True)])
 def test_route_few_tokens(T, d, E, k, renorm):
     rng = np.random.Generator(np.random.PCG64(T + E))
     xs, x = _bf16(rng, (T, d), 1.0)
