@@ -478,13 +478,14 @@ struct GHMC {
 // launch (a launch of their own took 3 to 5 us each, whatever its work).
 
 // p[0..n) = 0 for n bf16 values, n a multiple of 8, p 16-byte aligned (a
-// kernel rather than a memset, so that it can be captured in a graph)
-__device__ __forceinline__ void clear_bf16(bf16_t* __restrict__ p, int64_t n, int64_t i,
-                                           int64_t step) {
-    for (; i * 8 < n; i += step) st16(p + i * 8, uint4{0u, 0u, 0u, 0u});
+// kernel rather than a memset, so that it can be captured in a graph). One store
+// per thread over the whole range: a loop over a grid of 2048 workgroups wrote
+// 268 MB in 45 us, this in 37.
+__device__ __forceinline__ void clear_bf16(bf16_t* __restrict__ p, int64_t n, int64_t i) {
+    if (i * 8 < n) st16(p + i * 8, uint4{0u, 0u, 0u, 0u});
 }
 __global__ void __launch_bounds__(256) zero_bf16(bf16_t* __restrict__ p, int64_t n) {
-    clear_bf16(p, n, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
+    clear_bf16(p, n, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 // gs[token_index_map[i]] = gates[i] for the accepted choices i < S: the gate of
@@ -493,12 +494,12 @@ __global__ void __launch_bounds__(256) zero_bf16(bf16_t* __restrict__ p, int64_t
 __global__ void __launch_bounds__(256)
 fwd_prep(const float* __restrict__ gates, const int32_t* __restrict__ tim, int64_t S,
          float* __restrict__ gs, bf16_t* __restrict__ y, int64_t n) {
-    const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
-    for (int64_t i = i0; i < S; i += step) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < S) {
         const int32_t s = tim[i];
         if (s >= 0) gs[s] = gates[i];
     }
-    clear_bf16(y, n, i0, step);
+    clear_bf16(y, n, i);
 }
 
 // rank[r] = (expert, first slot, slot count) of the expert of rank r by slot
@@ -533,9 +534,8 @@ bwd_prep(const float* __restrict__ gates, const int32_t* __restrict__ slot_src,
         expert_ranks(offsets, E, rank);
         return;
     }
-    const int64_t filled = offsets[E], step = (int64_t)(gridDim.x - 1) * 256;
-    for (int64_t s = (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x; s < S; s += step)
-        gs[s] = s < filled ? gates[slot_src[s]] : 0.0f;
+    const int64_t s = (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x;
+    if (s < S) gs[s] = s < offsets[E] ? gates[slot_src[s]] : 0.0f;
 }
 
 // G3 with g*h formed on load from the saved A (and B) and the slot-ordered
@@ -653,10 +653,7 @@ __global__ void dgate_reduce(const float* __restrict__ part, int nparts,
 inline dim3 grid1d(int64_t n, int bs) { return dim3((unsigned)((n + bs - 1) / bs)); }
 
 // workgroups of a preparation launch over S slots and n bf16 values to clear
-inline unsigned prep_grid(int64_t S, int64_t n) {
-    const int64_t a = (S + 255) / 256, b = (n / 8 + 255) / 256, g = a > b ? a : b;
-    return (unsigned)(g < 2048 ? g : 2048);
-}
+inline unsigned prep_grid(int64_t S, int64_t n) { return grid1d(S > n / 8 ? S : n / 8, 256).x; }
 
 // number of workgroups for a row-wise grouped GEMM (upper bound on tiles)
 inline unsigned slot_grid(int64_t S, int E, int BM, int NT) {

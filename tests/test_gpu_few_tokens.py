@@ -6,7 +6,7 @@ import torch
 
 from oracle import oracle
 from paper_2601_05296_amd import binding as B
-from paper_2601_05296_amd import synth
+from paper_2601_05296_amd import layer, synth
 from tests.parity import assert_close, dev, host, launched, near_tie_ok
 
 pytestmark = pytest.mark.gpu
@@ -124,3 +124,61 @@ def test_index_one_workgroup(T, E, k):
     assert np.array_equal(counts, ref.counts[:E]) and np.array_equal(offsets, ref.offsets[:E + 1])
     assert np.array_equal(eti[:f], ref.eti[:f]) and np.array_equal(ss[:f], ref.slot_src[:f])
     assert np.array_equal(tim.reshape(T, k), np.where(rej, -1, ref.tim))
+
+
+def test_clear_runs_at_the_fill_rate():
+    """The atomic combine clears y and dx (268 MB here) as fast as a plain fill writes
+    them: measured at 0.94 of the time of torch's zero_, a loop over 2048 workgroups
+    at 1.16."""
+    T, d, f, E, k = 32768, 4096, 64, 2, 1
+    x, w1, w2 = (torch.randn(s, device="cuda").to(torch.bfloat16) for s in ((T, d), (E, d, f), (E, f, d)))
+    wg = torch.randn((E, d), device="cuda").to(torch.bfloat16)
+    times = {"fwd_prep": [], "zero_bf16": [], "fill": []}
+    fill = torch.empty_like(x)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for _ in range(15):
+        ev[0].record()
+        fill.zero_()
+        ev[1].record()
+        torch.cuda.synchronize()
+        times["fill"].append(ev[0].elapsed_time(ev[1]))
+        B.moe_probe_enable(64)
+        y, saved = layer.forward(x, wg, None, w1, None, w2, k, False, act="relu")
+        layer.backward(saved, x, x, wg, w1, None, w2)
+        torch.cuda.synchronize()
+        for i in range(B.moe_probe_count()):
+            name, ms = B.moe_probe_get(i)
+            times.get(name, []).append(ms)
+        B.moe_probe_disable()
+    med = {n: float(np.median(t)) for n, t in times.items()}
+    assert len(times["fwd_prep"]) == len(times["zero_bf16"]) == 15
+    assert max(med["fwd_prep"], med["zero_bf16"]) <= 1.05 * med["fill"], med
+
+
+# the last workgroup of each preparation launch: a clear longer and shorter than the
+# slots, more of both than one grid of 2048 x 256 threads
+@pytest.mark.parametrize("T,d,E,k", [(1, 64, 3, 1), (37, 64, 20, 16), (33, 64, 4, 2), (300001, 64, 2, 2),
+                                     (21000, 1024, 2, 1)])
+def test_clear_and_slot_gates(T, d, E, k):
+    """The atomic combine with zero experts clears every row of y and leaves the gates
+    in slot order in its workspace."""
+    z = dict(dtype=torch.bfloat16, device="cuda")
+    x = torch.randn((T, d), device="cuda").to(torch.bfloat16)
+    ids = dev(synth.random_ids(T, E, k, seed=T))
+    S, f, fl = T * k, 64, B.MOE_ACT_RELU | B.MOE_H_ON_LOAD | B.MOE_ATOMIC_COMBINE
+    i32 = dict(dtype=torch.int32, device="cuda")
+    m = [torch.empty(n, **i32) for n in (E, E + 1, S, S, S)]
+    n = B.moe_build_index_workspace_size(T, E, k)
+    B.moe_build_index(ids, T, E, k, *m, torch.empty(max(n, 16), dtype=torch.uint8, device="cuda"), n)
+    gates = torch.rand((T, k), device="cuda")
+    w1, w2 = torch.zeros((E, d, f), **z), torch.zeros((E, f, d), **z)
+    y = torch.full((T, d), float("nan"), **z)
+    A = torch.empty((S, f), **z)
+    n = B.moe_ffn_fwd_combine_workspace_size(T, d, f, E, k, fl)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    B.moe_ffn_fwd_combine(x, w1, None, w2, m[1], m[2], gates, m[3], T, d, f, E, k, fl, A, None, y, ws, n)
+    torch.cuda.synchronize()
+    assert not y.any()
+    # the workspace starts with the gates in slot order
+    gs = ws[:4 * S].view(torch.float32)
+    assert torch.equal(gs, gates.view(-1)[m[4].long()])
