@@ -124,9 +124,13 @@ void launch_combine(const void* src, int64_t src_ld, const float* w, const int32
     // most one wave per token instead, so that no lane idles and each lane
     // keeps more source loads in flight (measured faster on both).
     const bool pow2 = (nchunk & (nchunk - 1)) == 0;
-    // With few tokens the launch is bound by the latency of one lane's loop: a
-    // whole workgroup per token then (T = 1, k = 6, d = 2048: 9.3 us with one wave).
-    const int cap = T >= 2048 && (!pow2 || k > 4) ? WAVE : CMB_THREADS;
+    // With few tokens the launch is bound by the latency of one lane's loop: a whole
+    // workgroup per token then. One wave and a workgroup, us: d = 2048, k = 6: T = 1 (8.2,
+    // 6.2), 1000 (15.8, 8.0), 2047 (19.8, 15.4); d = 2880, k = 4: 1400 (18.0, 10.8), 2047
+    // (20.2, 16.1); d = 4096, k = 8: 2047 (49.6, 36.0); d = 1024, k = 16: 1400 (21.4, 15.0),
+    // 2047 (22.9, 26.9).
+    const bool few = T < 2048 && T * k < 24576;
+    const int cap = !few && (!pow2 || k > 4) ? WAVE : CMB_THREADS;
     int lpt_log2 = 0;
     while ((1 << lpt_log2) < nchunk && (1 << lpt_log2) < cap) ++lpt_log2;
     const int64_t tpb = CMB_THREADS >> lpt_log2;
