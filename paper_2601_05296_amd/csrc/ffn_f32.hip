@@ -269,13 +269,14 @@ f32_g2(const float* __restrict__ A, const float* __restrict__ B, const float* __
 
 // G4: u = dY[eti] W2[e]^T, dA and dB in place, and part[s][p] = the gate
 // gradient's sum of u * h over the columns of part p: column tiles p, p + P, ...
-// (P parts per slot; the tile lookup runs over the parts)
+// (P parts per slot; the tile lookup runs over the parts). P = 1: the whole sum,
+// straight into the gate gradients.
 template <int ACT>
 __global__ void __launch_bounds__(F_THREADS)
 f32_g4(const float* __restrict__ dy, const float* __restrict__ w2, const float* __restrict__ gates,
        const int32_t* __restrict__ offsets, const int32_t* __restrict__ eti,
        const int32_t* __restrict__ slot_src, int d, int f, int E, int P, float* __restrict__ A,
-       float* __restrict__ B, float* __restrict__ part) {
+       float* __restrict__ B, float* __restrict__ part, float* __restrict__ dgates) {
     __shared__ __align__(16) float lds[4 * TILE_F];
     __shared__ float red[2][FT];
     SlotTile t;
@@ -332,8 +333,11 @@ f32_g4(const float* __restrict__ dy, const float* __restrict__ w2, const float* 
     dg += __shfl_xor(dg, 32, 64);
     if ((threadIdx.x & 32) == 0) red[(threadIdx.x >> 6) & 1][f_row()] = dg;
     __syncthreads();
-    if ((int)threadIdx.x < t.mrows)
-        part[(row0 + threadIdx.x) * P + p0] = red[0][threadIdx.x] + red[1][threadIdx.x];
+    if ((int)threadIdx.x < t.mrows) {
+        const float sum = red[0][threadIdx.x] + red[1][threadIdx.x];
+        if (P == 1) dgates[slot_src[row0 + threadIdx.x]] = sum;
+        else part[(row0 + threadIdx.x) * P + p0] = sum;
+    }
 }
 
 // G6: dX_slot = dA W1[e]^T + dB W3[e]^T
@@ -478,15 +482,23 @@ hipError_t f32_bwd_act(const FfnArgs& a, hipStream_t st) {
                        a.offsets, a.eti, a.slot_src, a.d, a.f, (int)a.accumulate_dw, a.dw2);
     probe::mark("f32_g3", st);
     // dX_slot's space (the output, or the workspace of the combined call) holds
-    // the gate-gradient parts until G6 writes it: at most d parts per slot
+    // the gate-gradient parts until G6 writes it: at most d parts per slot. An
+    // output over dy or x, which G4 and G5 still read, holds nothing before G6: one
+    // part per slot then.
     float* dX = a.y ? static_cast<float*>(a.ws) : (float*)a.dX;
-    const int P = a.f / FT < a.d ? a.f / FT : a.d;
+    auto over = [&](const void* p) {
+        const uintptr_t b = reinterpret_cast<uintptr_t>(p), o = reinterpret_cast<uintptr_t>(dX);
+        return b < o + (size_t)S * a.d * 4 && o < b + (size_t)a.T * a.d * 4;
+    };
+    const int P = over(a.dy) || over(a.x) ? 1 : a.f / FT < a.d ? a.f / FT : a.d;
     hipLaunchKernelGGL(f32_g4<ACT>, dim3(f_grid(S, a.E, P)), dim3(F_THREADS), 0, st,
                        (const float*)a.dy, (const float*)a.w2, a.gates, a.offsets, a.eti,
-                       a.slot_src, a.d, a.f, a.E, P, (float*)a.A, (float*)a.B, dX);
+                       a.slot_src, a.d, a.f, a.E, P, (float*)a.A, (float*)a.B, dX, a.dgates);
     probe::mark("f32_g4", st);
-    if (hipError_t e = dgate_sum(dX, P, a.slot_src, a.offsets, a.E, S, a.dgates, st); e != hipSuccess)
-        return e;
+    if (P > 1) {
+        if (hipError_t e = dgate_sum(dX, P, a.slot_src, a.offsets, a.E, S, a.dgates, st); e != hipSuccess)
+            return e;
+    }
     hipLaunchKernelGGL(f32_g5, dim3(a.E * (a.d / FT) * (a.f / FT), ACT == ACT_SWIGLU ? 2 : 1),
                        dim3(F_THREADS), 0, st, (const float*)a.x, (const float*)a.A,
                        (const float*)a.B, a.offsets, a.eti, a.d, a.f, (int)a.accumulate_dw, a.dw1,

@@ -115,3 +115,44 @@ def test_ffn_f32_edges(counts, d, f, act):
     if gated:
         assert_close("dB", host(Bm), bw["dB"], "f32")
         assert_close("dw3", host(dw3), bw["dw3"] + base, "f32")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("over", ["dy", "x"])
+def test_dX_slot_in_place_of_an_input(dtype, over):
+    """Top-1: dX_slot [T, d] may take the place of dy or of x, which the backward has
+    finished with when it writes dX_slot."""
+    E, T, k, d, f = 5, 300, 1, 192, 320
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def n(*shape):
+        return torch.randn(shape, generator=gen, device="cuda").mul_(shape[-1] ** -0.5).to(dt)
+
+    ids = np.random.Generator(np.random.PCG64(1)).integers(0, E, (T, 1)).astype(np.int32)
+    ix = oracle.build_index(ids, E)
+    off, eti, ss = dev(ix.offsets), dev(ix.eti), dev(ix.slot_src)
+    x, dy, A0, B0 = n(T, d), n(T, d), n(T, f), n(T, f)
+    w1, w3, w2 = n(E, d, f), n(E, d, f), n(E, f, d)
+    g = torch.rand((T, 1), generator=gen, device="cuda")
+    fl = B.MOE_F32 if dtype == "f32" else 0
+    nws = B.moe_ffn_bwd_workspace_size(T, d, f, E, k, fl)
+    ws = torch.empty(max(nws, 16), dtype=torch.uint8, device="cuda")
+
+    def run(in_place):
+        f32 = dict(dtype=torch.float32, device="cuda")
+        o = dict(A=A0.clone(), B=B0.clone(), dw1=torch.empty((E, d, f), **f32),
+                 dw3=torch.empty((E, d, f), **f32), dw2=torch.empty((E, f, d), **f32),
+                 dg=torch.empty((T, 1), **f32))
+        xi, dyi = x.clone(), dy.clone()
+        o["dX"] = {"dy": dyi, "x": xi}[over] if in_place else torch.empty((T, d), dtype=dt, device="cuda")
+        B.moe_ffn_bwd(dyi, xi, w1, w3, w2, g, off, eti, ss, o["A"], o["B"], T, d, f, E, k, fl,
+                      o["dw1"], o["dw3"], o["dw2"], o["dg"], o["dX"], ws, nws)
+        torch.cuda.synchronize()
+        return o
+
+    apart, here = run(False), run(True)
+    # float32 adds the gate gradient's column tiles in another order
+    assert_close("d_gates", host(here.pop("dg")), host(apart.pop("dg")), "f32")
+    for name, t in apart.items():
+        assert torch.equal(t, here[name]), name
