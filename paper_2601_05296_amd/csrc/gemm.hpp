@@ -269,11 +269,10 @@ inline int wgrad_grid(int E, int MT, int NT) { return E * 8 * ((MT * NT + 7) / 8
 // sum: the grid is the worst case of one partial tile per expert, and dealing
 // out contiguous ranges of that grid left the last XCDs with padding while the
 // first had more than their share (one token, E = 64, k = 6: 66 tiles, all on
-// one XCD: layer forward 194 us, now 117; T = 1021 fwd + bwd 1281 -> 1156 us). With at
-// most 2% of padding there is little balance to gain, and the whole grid is
-// dealt out, in ranges of whole tile rows there (E = 8, S = 65536, 1.5% padding:
-// dX 13634 -> 13342 us; E = 128, S = 524288, 2.9%: the step takes 18310 us over
-// the tiles that exist against 18390 over the grid). Every
+// one XCD: layer forward 194 us, now 117; T = 1021 fwd + bwd 1281 -> 1156 us). It
+// holds with little padding too: E = 8, d = 4096, f = 14336, k = 2, all four
+// row-wise GEMMs over the grid and over the tiles that exist, us: T = 20000
+// 27089, 25351; 30000 (1.2% padding) 39754, 38400; 32768 43122, 42867. Every
 // thread of the block must call this;
 // `sh` is 8 ints of LDS, free on entry and again on return. Returns false past
 // the last tile.
@@ -315,11 +314,8 @@ __device__ bool find_slot_tile(int* sh, const int32_t* __restrict__ offsets, int
         total += sh[w];
         start += w < wv ? sh[w] : 0;
     }
-    const int pad = (int)gridDim.x - total;
-    const int n = pad * 50 <= (int)gridDim.x ? (int)gridDim.x : total;
-    if (bid >= n) return false;
-    bid = xcd_remap(bid, n);
     if (bid >= total) return false;
+    bid = xcd_remap(bid, total);
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
         if (bid >= start && bid < start + tiles[u]) {
