@@ -684,7 +684,6 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 //    r = 4: 68, the small tiles 68 to 113); below, small tiles while they run in
 //    one round (E = 8, d = 4096, f = 14336: r = 4 (345, 130), 75 (381, 280), 112
 //    (394, 491); one token of E = 64, d = 2048: (42, 18)).
-enum : int { SMALL_WIDE = 0, SMALL_NARROW = 1, SMALL_SLIM = 2 };
 inline int64_t est_rows(int64_t S, int E, int BM) {   // tile rows of BM
     const int64_t act = S < E ? S : E, full = (S + act * BM / 3) / BM;
     return act > full ? act : full;
@@ -700,7 +699,11 @@ inline int64_t est_rows(int64_t S, int E, int BM) {   // tile rows of BM
 //    258), 96 (312, 293), 159 (363, 386).
 inline bool few_tiles(int64_t tiles) { return tiles <= 128; }
 // first GEMM and dh GEMM: N = f, K = d; wide_cols and big_cols columns per tile
-// in the wide small tiles and in the 256-row ones
+// in the wide small tiles and in the 256-row ones. Beyond 112 rows per expert the
+// 128-row tiles while a 256-row grid would have up to 80 tiles, whose 128-row ones
+// run in one round with room for uneven experts. 256-row core and small core at 80,
+// 120 and about 140 tiles, us: first GEMM, E = 4, d = 4096, f = 2048 (86, 65), (89, 69),
+// (97, 125); dh GEMM, E = 2, d = 2048, f = 1408 (57, 45), (55, 43), (64, 86).
 inline SmallTile small_wide_n(int64_t S, int E, int ncols, int wide_cols, int big_cols) {
     const int64_t r = S / E;
     const bool few = est_rows(S, E, 256) * cdiv(ncols, big_cols) <= 80;

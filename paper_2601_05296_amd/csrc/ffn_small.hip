@@ -29,7 +29,7 @@ namespace {
 // Levels: WIDE reads the longest weight rows and is the best where its tiles
 // fill the chip; NARROW and SLIM halve the columns where they do not, and spend
 // the LDS on a deeper ring instead (one workgroup per CU).
-enum : int { WIDE = 0, NARROW = 1, SLIM = 2 };
+enum : int { WIDE = SMALL_WIDE, NARROW = SMALL_NARROW, SLIM = SMALL_SLIM };
 template <int BM, int LV> struct Sk;
 template <> struct Sk<32, WIDE> { using H = sk::Cfg<32, 256, 1, 4, 1, 4, 2>; };
 template <> struct Sk<32, NARROW> { using H = sk::Cfg<32, 128, 1, 4, 1, 6, 2>; };

@@ -1,9 +1,10 @@
 // gemm.hpp -- pieces shared by the grouped GEMM kernels, the router and the
-// router backward (gfx950): MFMA and LDS helpers, direct-to-LDS copies (used
-// by the router's ring), the 16-byte epilogue layout of a 32x32 accumulator
-// fragment, a wave's output coordinates, float32 tile output through LDS, and
-// the tile orders of the weight-gradient and the row-wise grouped GEMMs. The
-// GEMM main loop and its operand loaders are in gemm_rs.hpp.
+// router backward (gfx950): MFMA and LDS helpers, direct-to-LDS copies (the rings
+// of the router and of gemm_sk.hpp, the dh GEMM's epilogue), the 16-byte epilogue
+// layout of a 32x32 accumulator fragment, a wave's output coordinates, float32 tile
+// output through LDS, and the tile orders of the weight-gradient and the row-wise
+// grouped GEMMs. The main loops and their operand loaders are in gemm_rs.hpp and
+// gemm_sk.hpp.
 //
 // MFMA 32x32x16 operand layout (wave64), verified on gfx950: for D = P * Q,
 // lane L supplies P[L%32][8*(L/32) + 0..7] and Q[8*(L/32) + 0..7][L%32] and
@@ -55,14 +56,6 @@ __device__ __forceinline__ void lds_barrier() {
 // memory access may be issued inside it.
 __device__ __forceinline__ void dma16(const void* g, uint32_t lds_off) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 ::"v"(g), "s"(lds_off) : "memory", "m0");
-}
-
-// 4-byte global -> LDS copy by one lane: lane l writes LDS bytes
-// lds_off + 4*l .. +3 (same rules as dma16; the source needs only 4-byte
-// alignment).
-__device__ __forceinline__ void dma4(const void* g, uint32_t lds_off) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
                  ::"v"(g), "s"(lds_off) : "memory", "m0");
 }
 

@@ -75,8 +75,8 @@ hipError_t f32_fwd(const FfnArgs& a, hipStream_t st);
 hipError_t f32_bwd(const FfnArgs& a, hipStream_t st);
 
 // ---- row-wise GEMMs for few rows per expert (ffn_small.hip) ----
-// rows per tile (32, 64 or 128; 0: not these kernels) and column level (0 wide,
-// 1 narrow, 2 slim)
+// rows per tile (32, 64 or 128; 0: not these kernels) and column level
+enum : int { SMALL_WIDE = 0, SMALL_NARROW = 1, SMALL_SLIM = 2 };
 struct SmallTile { int rows, level; };
 hipError_t small_first(const FfnArgs& a, SmallTile v, void* H, hipStream_t st);
 // columns [c0, c0 + nc) of the second GEMM from H, or (H null; 32 or 64 rows)
