@@ -404,28 +404,44 @@ def kernel_model(name, cfg, elem, recompute=False):
     T, d, f, E, k = cfg.T, cfg.d, cfg.f, cfg.E, cfg.k
     S = T * k
     g = 2.0 * S * d * f  # flops of one [S x d] x [d x f] product
-    if name.startswith("sk_g"):   # the same GEMM in its small-row tiles
-        name = name[3:] + "_kernel"
     nb = 2 if cfg.act == "swiglu" else 1   # right operands of g1, g5, g6
-    flops = {"g1_kernel": nb * g * (2 if recompute else 1), "g2_kernel": g, "g2h_kernel": g,
+    runs = 2 if recompute else 1           # of the first GEMM and the index build
+    small = name.startswith("sk_g")             # the same GEMM in its small-row tiles
+    name = name[3:] + "_kernel" if small else name.replace("_narrow", "_kernel")
+    flops = {"g1_kernel": nb * g * runs, "g2_kernel": g, "g2h_kernel": g,
              "g3_kernel": g, "g3h_kernel": g,
              "g4_kernel": g, "g5_kernel": nb * g, "g6_kernel": nb * g}
+    if small:
+        # the weights of the experts with tokens read once, the rows in and out;
+        # whichever bound is the longer
+        mat = E * (1.0 - (1.0 - k / E) ** T) * d * f * elem
+        byts = {"g1_kernel": runs * (nb * (mat + S * f * elem) + T * d * elem),
+                "g2_kernel": mat + S * (f + d) * elem, "g2h_kernel": mat + S * (nb * f + d) * elem,
+                "g4_kernel": mat + T * d * elem + 2 * nb * S * f * elem,
+                "g6_kernel": nb * (mat + S * f * elem) + S * d * elem}
+        if byts[name] / PEAK_HBM_GBS * 1e3 > flops[name] / PEAK_BF16_TFLOPS:
+            return float(byts[name]), "GB/s", "hbm"
     if name in flops:
         return flops[name], "TFLOP/s", "mfma"
     nparts = -(-f // 256) * 4   # gate-gradient partials per slot (G4: 256-column tiles, 4 waves across)
-    nbuild = 2 if recompute else 1   # full recompute builds the maps again in the backward
     byts = {
         "route_bf16": T * d * elem + E * d * elem + T * E * 4 + T * k * 8,
-        "tile_hist": nbuild * S * 4,
+        "route_f32": T * d * elem + E * d * elem + T * E * 4 + T * k * 8,
+        "route_logits": T * d * elem + E * d * elem + T * E * 4,
+        "route_pick": T * E * 4 + T * k * 8,
+        "tile_hist": runs * S * 4,
         "tile_scan": 0,
-        "tile_rank": nbuild * (S * 4 + 3 * S * 4),
+        "tile_rank": runs * (S * 4 + 3 * S * 4),
         "combine": 2 * (S * d * elem + T * d * elem + T * k * 8),   # forward and backward
         "dgate_reduce": S * nparts * 4 + S * 8,
-        "index_one": nbuild * (S * 4 + 3 * S * 4),
+        "combine_f32": 2 * (S * d * elem + T * d * elem + T * k * 8),
+        "index_one": runs * (S * 4 + 3 * S * 4),
         "fwd_prep": S * 12 + T * d * elem,   # slot gates, y cleared
         "bwd_prep": E * 4 + E * 16 + S * 12,
         "zero_bf16": T * d * elem,           # dx
         "rb_dlogits": T * E * 4 * 2 + T * k * 12,
+        "rb_dx": T * E * 4 + E * d * elem + 2 * T * d * elem,   # float32
+        "rb_dwg_partial": T * E * 4 + T * d * elem,            # float32
         "rb_products": 2 * T * E * 4 + E * d * elem + 3 * T * d * elem,
         "rb_dwg_reduce": 0,
     }

@@ -857,9 +857,10 @@ hipError_t ffn_fwd_act(const FfnArgs& a, hipStream_t st) {
                                    (const bf16_t*)a.B, (const bf16_t*)a.w2, a.offsets, a.d, a.f,
                                    a.E, c0, nc, ldo, out, a.eti, gs);
             };
-            if (few_tiles(est_rows(S, a.E, RHW::BM) * cdiv(nc, RHW::BN))) run(RHN{});
+            const bool few = few_tiles(est_rows(S, a.E, RHW::BM) * cdiv(nc, RHW::BN));
+            if (few) run(RHN{});
             else run(RHW{});
-            probe::mark("g2h_kernel", st);
+            probe::mark(few ? "g2h_narrow" : "g2h_kernel", st);
         } else {
             auto g2 = gs ? g2_kernel<true> : g2_kernel<false>;
             hipLaunchKernelGGL(g2, dim3(slot_grid(S, a.E, RS::BM, cdiv(nc, RS::BN))),
@@ -985,9 +986,10 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
                                dim3(C::THREADS), C::LDS, st, (const bf16_t*)a.A, (const bf16_t*)Bx,
                                (const float*)gs, (const bf16_t*)a.dy, rank, a.eti, a.d, a.f, a.dw2);
         };
-        if (few_tiles((int64_t)a.E * cdiv(a.f, RHW::BM) * cdiv(a.d, RHW::BN))) run(RHN{});
+        const bool few = few_tiles((int64_t)a.E * cdiv(a.f, RHW::BM) * cdiv(a.d, RHW::BN));
+        if (few) run(RHN{});
         else run(RHW{});
-        probe::mark("g3h_kernel", st);
+        probe::mark(few ? "g3h_narrow" : "g3h_kernel", st);
     }
     const SmallTile t4 = small_wide_n(S, a.E, a.f, 256, RS::BN);
     if (t4.rows) {
@@ -1011,9 +1013,10 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
                                dim3(C::THREADS), C::LDS, st, (const bf16_t*)HG,
                                (const bf16_t*)a.dy, rank, a.eti, a.d, a.f, a.dw2);
         };
-        if (few_tiles((int64_t)a.E * cdiv(a.f, RS::BM) * cdiv(a.d, RS::BN))) run(RSN{});
+        const bool few = few_tiles((int64_t)a.E * cdiv(a.f, RS::BM) * cdiv(a.d, RS::BN));
+        if (few) run(RSN{});
         else run(RS{});
-        probe::mark("g3_kernel", st);
+        probe::mark(few ? "g3_narrow" : "g3_kernel", st);
     }
     auto dw13 = [&](auto cfg) {
         using C = decltype(cfg);
@@ -1022,11 +1025,11 @@ hipError_t ffn_bwd_act(const FfnArgs& a, hipStream_t st) {
                            dim3(C::THREADS), C::LDS, st, (const bf16_t*)a.x, (const bf16_t*)a.A,
                            (const bf16_t*)a.B, rank, a.eti, a.d, a.f, a.dw1, a.dw3);
     };
-    if (S / a.E <= 96 ||
-        few_tiles((int64_t)a.E * cdiv(a.d, CFirst<ACT>::BM) * cdiv(a.f, CFirst<ACT>::BN)))
-        dw13(CNarrow<ACT>{});
+    const bool few5 = S / a.E <= 96 ||
+        few_tiles((int64_t)a.E * cdiv(a.d, CFirst<ACT>::BM) * cdiv(a.f, CFirst<ACT>::BN));
+    if (few5) dw13(CNarrow<ACT>{});
     else dw13(CFirst<ACT>{});
-    probe::mark("g5_kernel", st);
+    probe::mark(few5 ? "g5_narrow" : "g5_kernel", st);
     const int kslices = (GATED ? 2 : 1) * a.f / rs::KS;
     auto t6 = [&](int nc) { return small_long_k(S, a.E, nc); };
     if (!a.y && t6(a.d).rows) return small_dx(a, t6(a.d), 0, a.d, (int64_t)a.d, a.dX, false, st);
