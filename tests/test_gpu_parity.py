@@ -8,7 +8,7 @@ import torch
 from oracle import oracle
 from paper_2601_05296_amd import binding as B
 from paper_2601_05296_amd import layer, synth
-from tests.parity import TOL, assert_close, dev, host, near_tie_ok, rel_err
+from tests.parity import TOL, assert_close, dev, host, launched, near_tie_ok, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -108,7 +108,9 @@ def _sink_index(ids, rej, E):
 
 @pytest.mark.parametrize("T,E,k,frac", [
     (300, 8, 2, 0.2), (1000, 64, 6, 0.3), (777, 256, 16, 0.5), (513, 16, 4, 1.0), (1, 4, 2, 1.0),
-    (200, 8, 3, None)])
+    (200, 8, 3, None),
+    # past one workgroup's 1024 tokens: the three-launch build
+    (5000, 256, 16, 0.5), (3001, 16, 4, 1.0), (2000, 8, 3, None), (70001, 64, 6, 0.3)])
 def test_build_index_rejects_invalid_ids(T, E, k, frac):
     if frac is None:   # every choice rejected
         ids = np.full((T, k), -1, np.int32)
@@ -132,7 +134,24 @@ def test_build_index_rejects_invalid_ids(T, E, k, frac):
     ("bf16", "relu", False, True), ("f32", "swiglu", False, False),
     ("bf16", "swiglu", True, "atomic"), ("bf16", "silu", False, "atomic")])
 def test_ffn_with_rejected_choices(dtype, act, h_on_load, combined):
-    T, d, f, E, k = 300, 256, 384, 8, 3
+    _check_ffn_with_rejected_choices(dtype, act, h_on_load, combined, 300, 256, 384, 8, 3)
+
+
+@pytest.mark.parametrize("act,h_on_load,combined", [
+    ("swiglu", False, True), ("swiglu", True, "atomic"), ("silu", True, False),
+    ("relu", False, "atomic"), ("swiglu", True, False)])
+def test_large_tiles_with_rejected_choices(act, h_on_load, combined):
+    """The 256-row GEMMs and the large weight-gradient tiles, element by element,
+    with partial tiles in rows and columns and rejected choices (the many small
+    shapes of this file select the tiles for few rows or few tiles)."""
+    names = launched(lambda: _check_ffn_with_rejected_choices("bf16", act, h_on_load, combined,
+                                                              5700, 320, 448, 48, 3))
+    second = {"g2h_kernel", "g3h_kernel"} if h_on_load else {"g2_kernel", "g3_kernel"}
+    gemms = {n for n in names if n.startswith(("g1", "g2", "g3", "g4", "g5", "g6", "sk_"))}
+    assert gemms == {"g1_kernel", "g4_kernel", "g5_kernel", "g6_kernel"} | second
+
+
+def _check_ffn_with_rejected_choices(dtype, act, h_on_load, combined, T, d, f, E, k):
     inp, _, g = _layer_case(dtype, T, d, f, E, k, False, None)
     ids = _corrupt_ids(T, E, k, seed=3, frac=0.3)
     ids[:5] = -1                      # tokens with no valid choice at all
@@ -296,7 +315,11 @@ def test_route_parity(dtype, T, d, E, k, renorm, bias):
     # per-token array bounds 4 / 8 / 16 (the kernel is sized by the smallest
     # bound >= k): both sides of each edge, and bf16 rows wider than 256 chunks
     ("bf16", 129, 256, 4, True, False), ("bf16", 200, 4096, 5, False, True),
-    ("bf16", 300, 1024, 12, True, True), ("f32", 150, 512, 3, True, False)])
+    ("bf16", 300, 1024, 12, True, True), ("f32", 150, 512, 3, True, False),
+    # one wave per token: from 2048 tokens, and from 24576 sources, with more than
+    # four sources or a chunk count that is no power of two
+    ("bf16", 2049, 768, 6, True, False), ("bf16", 2500, 640, 3, False, True),
+    ("bf16", 1537, 1024, 16, True, False), ("f32", 2100, 320, 5, True, True)])
 def test_combine_parity(dtype, T, d, k, weighted, accumulate):
     rng = np.random.default_rng(T + d + k)
     E = max(k, 8)

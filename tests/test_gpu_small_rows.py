@@ -9,7 +9,7 @@ import torch
 
 from oracle import oracle
 from paper_2601_05296_amd import binding as B
-from tests.parity import dev
+from tests.parity import dev, launched
 
 pytestmark = pytest.mark.gpu
 
@@ -92,11 +92,17 @@ EDGES_128 = [97, 127, 128, 129, 1, 64, 65, 100]        # mean 88: 128-row tiles
     (EDGES_128 * 12, 576, 576, "swiglu", False, False),
     (EDGES_128 * 12, 64, 64, "swiglu", True, True),
     # many rows of few experts: launches that leave CUs idle in the large tiles
-    # (dX and second GEMM in 64- and 128-row tiles, h on load in 64 x 512, weight
-    # gradients in 128 x 128)
     ([700, 513], 320, 576, "swiglu", True, False),
     ([2049, 1, 1500], 192, 704, "silu", False, False),
-    ([6000, 5000], 576, 192, "relu", True, True)])
+    # ... h on load in 64 x 512 tiles, dX in 128-row tiles
+    ([6000, 5000], 448, 192, "relu", True, True), ([6000, 5000], 448, 192, "swiglu", True, False),
+    ([9000, 4100], 64, 128, "silu", True, True), ([9000, 4100], 64, 128, "silu", True, False),
+    ([9000, 4100], 64, 128, "relu", True, False), ([9000, 4100], 64, 128, "swiglu", True, True)] + [
+    # h formed on load in 32-row tiles of 128 and of 256 columns and in 64-row tiles of
+    # 128 and of 256
+    ([n] * E, d, 128, act, True, atomic)
+    for E, n, d in ((24, 20, 768), (40, 20, 832), (24, 29, 768), (40, 29, 832))
+    for act in ("swiglu", "silu", "relu") for atomic in (False, True)])
 def test_small_rows_same_bits(counts, d, f, act, h_on_load, atomic):
     E, T = len(counts), sum(counts)
     rng = np.random.Generator(np.random.PCG64(T + d + f))
@@ -105,12 +111,27 @@ def test_small_rows_same_bits(counts, d, f, act, h_on_load, atomic):
     w = (_bf16(rng, (E, d, f), d ** -0.5), _bf16(rng, (E, d, f), d ** -0.5),
          _bf16(rng, (E, f, d), f ** -0.5))
     gates = torch.from_numpy(rng.random((T, 1), dtype=np.float32)).cuda()
-    one = _ffn(ids, gates, x, dy, w, act, h_on_load, atomic)
+    one, rep = {}, {}
+    few = launched(lambda: one.update(_ffn(ids, gates, x, dy, w, act, h_on_load, atomic)))
     # repeats for a mean of 300 rows per expert and 130 row tiles of 256, beyond
     # every rule of the small kernels
     n = -(-max(300 * E, 130 * 256) // T)
-    rep = _ffn(np.tile(ids, (n, 1)), gates.repeat(n, 1), x.repeat(n, 1), dy.repeat(n, 1), w, act,
-               h_on_load, atomic)
+    many = launched(lambda: rep.update(_ffn(np.tile(ids, (n, 1)), gates.repeat(n, 1),
+                                            x.repeat(n, 1), dy.repeat(n, 1), w, act, h_on_load,
+                                            atomic)))
+    # the two runs take different kernels in every row-wise GEMM: G1, the second, G4, dX
+    # (G1 of 6000 and 5000 rows in 64 + 64 columns has too many tiles for the small ones)
+    gemms = ("g1", "g2", "g2h", "g4", "g6")
+    few = [k for k in few if k.replace("sk_", "").split("_")[0] in gemms]
+    many = [k for k in many if k.replace("sk_", "").split("_")[0] in gemms]
+    assert many == ["g1_kernel", "g2h_kernel" if h_on_load else "g2_kernel", "g4_kernel", "g6_kernel"]
+    second = ("sk_g2h", "g2h_narrow") if h_on_load else ("sk_g2",)
+    assert few[1] in second and few[2:] == ["sk_g4", "sk_g6"], few
+    if max(counts) > 4000:
+        assert few[1] == "g2h_narrow"
+    elif len(set(counts)) == 1:
+        assert few[1] == "sk_g2h"
+    assert few[0] == "sk_g1" or (act == "swiglu" and max(counts) == 6000), few
     for name, a in one.items():
         assert torch.isfinite(a.float()).all(), name
         assert torch.equal(a, rep[name][:T]), name
