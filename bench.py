@@ -201,10 +201,11 @@ def summarize_stats(stats_csv, out, workload, cmd, profile_cmd):
     """Per-kernel calls and durations from rocprofv3's kernel_stats.csv."""
     import csv
     from paper_2601_05296_amd import synth
-    cfg = synth.CONFIGS[workload]
+    cfg = synth.CONFIGS.get(workload)   # or the name of a case of perf/cases.py
     rows = list(csv.DictReader(open(stats_csv)))
-    lines = ["# rocprofv3 kernel statistics, workload %s (T=%d d=%d f=%d E=%d k=%d, %s)"
-             % (workload, cfg.T, cfg.d, cfg.f, cfg.E, cfg.k, cfg.dtype),
+    lines = ["# rocprofv3 kernel statistics, workload %s" % workload +
+             (" (T=%d d=%d f=%d E=%d k=%d, %s)" % (cfg.T, cfg.d, cfg.f, cfg.E, cfg.k, cfg.dtype)
+              if cfg else ""),
              "# profile: %s" % profile_cmd,
              "# summary: python %s" % cmd,
              "# kernel calls avg_us total_ms pct min_us max_us"]

@@ -22,8 +22,8 @@
  *      w1, w3   [E, d, f]      expert first layer: SiLU branch, linear branch
  *      w2       [E, f, d]      expert down projection
  *    Element type of x, w_gate, w1, w3, w2, dy, A, B, O, dX_slot and the
- *    y / dx outputs: bfloat16 (MOE_BF16, the default) or float32 (MOE_F32,
- *    a debug mode). Gates, logits, gate gradients and weight gradients are
+ *    y / dx outputs: bfloat16 (MOE_BF16, the default) or float32 (MOE_F32).
+ *    Gates, logits, gate gradients and weight gradients are
  *    float32 in both modes; index arrays are int32.
  *  - A slot is one (token, chosen expert) pair; there are S = T*k slots,
  *    grouped by expert and, inside an expert, by ascending token id.
@@ -53,7 +53,7 @@ extern "C" {
 
 /* flags (bitwise or) */
 #define MOE_BF16        0u   /* bfloat16 activations and weights (default) */
-#define MOE_F32         1u   /* float32 activations and weights (debug mode) */
+#define MOE_F32         1u   /* float32 activations and weights */
 #define MOE_RENORM      2u   /* moe_route / moe_route_bwd: renormalise the k gates */
 #define MOE_ACCUMULATE  4u   /* moe_combine / moe_route_bwd: add into the output */
 /* moe_ffn_fwd / moe_ffn_bwd: expert activation. Default (neither flag): the

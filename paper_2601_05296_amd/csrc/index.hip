@@ -23,6 +23,8 @@
 //                   ascending token order inside every expert, as in the
 //                   paper's worked example, and the result is deterministic.
 //
+// Up to 1024 tokens one workgroup does all of it in one launch (index_one).
+//
 // A choice whose id lies outside [0, E) or repeats an earlier id of its row
 // (top-k never produces either) is rejected by both passes alike: it gets no
 // slot and its token_index_map entry is -1. Every slot below offsets[E] is
@@ -46,7 +48,6 @@ namespace {
 constexpr int IDX_THREADS = 256;
 constexpr int MAX_TILES = 1024;
 
-// tokens per tile: a multiple of 256 keeping the number of tiles <= MAX_TILES
 // does choice j of a row take a slot: its id is in [0, E) and differs from the
 // ids of the row's earlier choices
 __device__ inline bool choice_ok(const int32_t* row, int j, int E) {
@@ -57,6 +58,7 @@ __device__ inline bool choice_ok(const int32_t* row, int j, int E) {
     return true;
 }
 
+// tokens per tile: a multiple of 256 keeping the number of tiles <= MAX_TILES
 inline int64_t tile_tokens(int64_t T) {
     int64_t tb = (T + MAX_TILES - 1) / MAX_TILES;
     tb = ((tb + IDX_THREADS - 1) / IDX_THREADS) * IDX_THREADS;

@@ -5,7 +5,7 @@ import torch
 from paper_2601_05296_amd import binding as B
 
 # Tolerance on max|gpu - ref| / max|ref| per tensor: bf16 storage with float32
-# accumulation, and the float32 debug mode.
+# accumulation, and the float32 mode.
 TOL = {"bf16": 2e-2, "f32": 1e-4}
 
 

@@ -103,7 +103,7 @@ def test_h_on_load_flag():
             lib.moe_ffn_bwd_workspace_size(T, d, f, E, k, fl | B.MOE_H_ON_LOAD) >= h - (S + 64) * 4 - 256
         assert lib.moe_ffn_bwd_combine_workspace_size(T, d, f, E, k, fl | B.MOE_H_ON_LOAD) <= \
             lib.moe_ffn_bwd_combine_workspace_size(T, d, f, E, k, fl)
-    # float32 debug mode buffers no h either way
+    # float32 mode buffers no h either way
     assert lib.moe_ffn_fwd_workspace_size(T, d, f, E, k, B.MOE_F32 | B.MOE_H_ON_LOAD) == \
         lib.moe_ffn_fwd_workspace_size(T, d, f, E, k, B.MOE_F32)
     # without h the separate forward needs no workspace at all
