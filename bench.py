@@ -23,6 +23,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -157,9 +158,18 @@ def traffic_path(workload):
 
 
 def kernel_short_name(full: str) -> str:
-    """'void moe::(anonymous namespace)::g5_kernel(...)' -> 'g5_kernel'."""
-    name = full.replace("(anonymous namespace)", "")
-    return name.split("(")[0].split("::")[-1].split("<")[0].split()[-1]
+    """'void moe::(anonymous namespace)::g5_kernel<...>(...)' -> 'g5_kernel', the
+    tiles for few of them 'g5_narrow' (the names the library's probe records)."""
+    name, depth = "", 0
+    for ch in full.replace("(anonymous namespace)", ""):   # without template arguments
+        depth += (ch == "<") - (ch == ">")
+        if depth == 0 and ch != ">":
+            name += ch
+    name = name.split("(")[0].split("::")[-1].split()[-1]
+    if name in ("g2h_kernel", "g3_kernel", "g3h_kernel", "g5_kernel") and \
+            re.search(r"Cfg<(64, 512|128, 128|128, 64),", full):
+        name = name.replace("_kernel", "_narrow")
+    return name
 
 
 def summarize_pmc(fetch_csv, write_csv, out, workload, cmd):

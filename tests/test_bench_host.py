@@ -56,3 +56,20 @@ def test_small_row_gemms_are_priced_by_their_bound():
     assert (unit, bound) == ("GB/s", "hbm") and weights < amount < 1.02 * weights
     many = synth.CONFIGS["mid_e64k6"]
     assert bench.kernel_model("sk_g1", many, 2) == bench.kernel_model("g1_kernel", many, 2)
+
+
+def test_kernel_short_names():
+    """Profiler names without namespaces, parameters and template arguments, also
+    where an argument is a type of the namespace."""
+    ns = "moe::(anonymous namespace)::"
+    for full, short in (
+            ("void %sg5_kernel<0, moe::rs::Cfg<256, 128, 2, 4, 2>, false>(unsigned short const*, int)" % ns, "g5_kernel"),
+            ("void %sg5_kernel<0, moe::rs::Cfg<128, 64, 2, 2, 2>, true>(float*)" % ns, "g5_narrow"),
+            ("void %sg2h_kernel<1, true, moe::rs::Cfg<64, 512, 1, 8, 1> >(int)" % ns, "g2h_narrow"),
+            ("void %sg3h_kernel<0, moe::rs::Cfg<128, 512, 2, 4, 1>, false>(int)" % ns, "g3h_kernel"),
+            ("void %ssk_g2<0, true, false, %sSk<32, 2> >(unsigned short const*, long)" % (ns, ns), "sk_g2"),
+            ("%sroute_pick(float const*, long)" % ns, "route_pick"),
+            ("__amd_rocclr_copyBuffer", "__amd_rocclr_copyBuffer"),
+            ("void at::native::vectorized_elementwise_kernel<4, at::native::FillFunctor<float>, "
+             "std::array<char*, 1ul> >(int, at::native::FillFunctor<float>)", "vectorized_elementwise_kernel")):
+        assert bench.kernel_short_name(full) == short, full
