@@ -8,8 +8,8 @@
 // One layer forward with E = 64, d = 2048, f = 1408, k = 6: first GEMM with one
 // token 44 -> 18 us, with 48 tokens (all 64 experts, 739 MB of weights) 149 ->
 // 124 us, that is 6.0 TB/s (kernel trace: 126, 121 at best). E = 128, d = f = 2880, 300
-// tokens (4.2 GB): 808 -> 696 us. The rule that chooses between the cores, with both sides measured, is
-// at small_wide_n and its neighbours in ffn.hip.
+// tokens (4.2 GB): 808 -> 696 us. The rule that chooses between the cores, with
+// both sides measured, is at small_wide_n and its neighbours in ffn.hip.
 #include "common.hpp"
 #include "ffn_epi.hpp"
 #include "gemm.hpp"
