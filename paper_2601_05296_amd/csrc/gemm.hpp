@@ -266,7 +266,7 @@ inline int wgrad_grid(int E, int MT, int NT) { return E * 8 * ((MT * NT + 7) / 8
 // holds with little padding too: E = 8, d = 4096, f = 14336, k = 2, all four
 // row-wise GEMMs over the grid and over the tiles that exist, us: T = 20000
 // 27089, 25351; 30000 (1.2% padding) 39754, 38400; 32768 equal within 0.5% (either
-// way, by box). Every thread of the block must call this; `sh` is 8 ints of LDS,
+// way, by card). Every thread of the block must call this; `sh` is 8 ints of LDS,
 // free on entry and again on return. Returns false past the last tile.
 struct SlotTile {
     int e;       // expert
